@@ -1043,6 +1043,22 @@ __device__ __forceinline__ float mean_intensity(const FinalizeArgs& a, int64_t p
   return static_cast<float>((static_cast<double>(a.moments[p]) - a.moments[np + p]) / a.count);
 }
 
+// The 8 results from the sums over the grid, the region and the fit.
+__device__ __forceinline__ void finalize_write(const FinalizeArgs& a, double m1_sum, double r2m1, double si_sum,
+                                               double w_sum, float thr, double s0, double sx, double sxx, double sy,
+                                               double sxy) {
+  const double den = s0 * sxx - sx * sx;
+  const double slope = den != 0 ? (s0 * sxy - sx * sy) / den : 0.0;
+  a.summary[0] = w_sum != 0 ? si_sum / w_sum : 0.0;
+  a.summary[1] = m1_sum > 0 ? sqrt(2.0 * r2m1 / m1_sum) : 0.0;
+  a.summary[2] = slope < 0 ? sqrt(-2.0 / slope) : __builtin_huge_val();
+  a.summary[3] = a.count;
+  a.summary[4] = si_sum;
+  a.summary[5] = w_sum;
+  a.summary[6] = a.power_fraction > 0 ? static_cast<double>(thr) : 0.0;
+  a.summary[7] = 0.0;
+}
+
 __global__ __launch_bounds__(1024) void finalize_kernel(FinalizeArgs a) {
   constexpr int NT = 1024;
   __shared__ double red[NT];
@@ -1125,18 +1141,232 @@ __global__ __launch_bounds__(1024) void finalize_kernel(FinalizeArgs a) {
   sxx = block_sum<NT>(sxx, red);
   sy = block_sum<NT>(sy, red);
   sxy = block_sum<NT>(sxy, red);
-  if (threadIdx.x == 0) {
-    const double den = s0 * sxx - sx * sx;
-    const double slope = den != 0 ? (s0 * sxy - sx * sy) / den : 0.0;
-    a.summary[0] = w_sum != 0 ? si_sum / w_sum : 0.0;
-    a.summary[1] = m1_sum > 0 ? sqrt(2.0 * r2m1 / m1_sum) : 0.0;
-    a.summary[2] = slope < 0 ? sqrt(-2.0 / slope) : __builtin_huge_val();
-    a.summary[3] = a.count;
-    a.summary[4] = si_sum;
-    a.summary[5] = w_sum;
-    a.summary[6] = a.power_fraction > 0 ? static_cast<double>(thr) : 0.0;
-    a.summary[7] = 0.0;
+  if (threadIdx.x == 0) finalize_write(a, m1_sum, r2m1, si_sum, w_sum, thr, s0, sx, sxx, sy, sxy);
+}
+
+// ---------------------------------------------------------------------------
+// The same statistics over many blocks.  One block reads the moments with one
+// CU (a full pass over 1024 x 1024 sums takes it about 0.35 ms, the bisection
+// 31 such passes: 13.5 ms in all); spread over the chip every pass is a few
+// microseconds, bound by launch latency.  Partial sums need memory that a
+// caller's 8-word summary does not have, so the SI map, written last, holds
+// them until then.  The sums are FP64 in a fixed order (thread, wave, block),
+// the same bits on every run; S(t), the power above a threshold, is added up
+// in the order of the total, so S(0) is the total exactly.
+//   finalize_sums     sum m1, sum r^2 m1, sum of m1 in FP32, max m1
+//   finalize_bracket  S(t) at 15 thresholds that split the bracket of bit
+//                     patterns in 16; 8 passes bring the 2^31 patterns to one
+//   finalize_region   the SI sums over the region, the sums of the fit
+//   finalize_summary  the 8 results
+//   finalize_map      the SI map, over the scratch
+// ---------------------------------------------------------------------------
+constexpr int kFinThreads = 1024;
+constexpr int kFinWaves = kFinThreads / 64;
+constexpr int kFinSplit = 16;    // pieces a pass splits the bracket into
+constexpr int kFinPasses = 8;    // 16^8 > 0x7F800000
+constexpr int kFinMaxBlocks = 256;
+static_assert(kFinSplit - 1 <= kFinWaves && 8 <= kFinWaves, "a wave joins each sum");
+
+// Blocks for np pixels, four per thread until every CU has a block.
+constexpr int finalize_blocks(int64_t np) {
+  return np / (4 * kFinThreads) < 1 ? 1
+                                    : (np / (4 * kFinThreads) > kFinMaxBlocks ? kFinMaxBlocks
+                                                                              : static_cast<int>(np / (4 * kFinThreads)));
+}
+
+// The scratch (doubles): per-block sums of the first pass [4][nb], of the
+// region [7][nb], of two alternating bracket passes [2][16][nb], and the
+// bracket each pass starts from [passes + 1][2].
+struct FinScratch {
+  double *first, *region, *split, *bracket;
+  int nb;
+};
+__host__ __device__ inline FinScratch finalize_scratch(double* base, int nb) {
+  return FinScratch{base, base + 4 * nb, base + 11 * nb, base + (11 + 2 * kFinSplit) * nb, nb};
+}
+constexpr int64_t finalize_scratch_bytes(int nb) {
+  return static_cast<int64_t>(sizeof(double)) * ((11 + 2 * kFinSplit) * nb + 2 * (kFinPasses + 1));
+}
+
+// Join v[0..C) over the block into out[c * nb + block]; in wave, then wave order.
+template <int C, class Op>
+__device__ __forceinline__ void finalize_join(double (&v)[C], double* out, int nb, double (&red)[kFinWaves * kFinSplit],
+                                              Op op) {
+  const int wave = threadIdx.x / 64;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v[c] = op(c, v[c], __shfl_xor(v[c], off));
+  if (threadIdx.x % 64 == 0) {
+#pragma unroll
+    for (int c = 0; c < C; ++c) red[wave * kFinSplit + c] = v[c];
   }
+  __syncthreads();
+  if (threadIdx.x < C) {
+    const int c = threadIdx.x;
+    double s = red[c];
+    for (int w = 1; w < kFinWaves; ++w) s = op(c, s, red[w * kFinSplit + c]);
+    out[static_cast<size_t>(c) * nb + blockIdx.x] = s;
+  }
+}
+
+// Join the blocks' values of `count` quantities (one wave each) into tot[]; every block
+// gets the same bits.  Block-wide barrier at the end.
+template <class Op>
+__device__ __forceinline__ void finalize_totals(const double* part, int nb, int count, double* tot, Op op) {
+  const int c = threadIdx.x / 64, lane = threadIdx.x % 64;
+  if (c < count) {
+    const double* p = part + static_cast<size_t>(c) * nb;
+    double s = lane < nb ? p[lane] : 0.0;
+    for (int i = lane + 64; i < nb; i += 64) s = op(c, s, p[i]);
+    for (int off = 32; off > 0; off >>= 1) s = op(c, s, __shfl_xor(s, off));
+    if (lane == 0) tot[c] = s;
+  }
+  __syncthreads();
+}
+
+struct FinAdd {
+  __device__ __forceinline__ double operator()(int, double a, double b) const { return a + b; }
+};
+// quantity 3 of the first pass is a maximum (of non-negative values; NaN ignored, as fmax does)
+struct FinFirst {
+  __device__ __forceinline__ double operator()(int c, double a, double b) const { return c == 3 ? fmax(a, b) : a + b; }
+};
+
+__global__ __launch_bounds__(kFinThreads) void finalize_sums_kernel(FinalizeArgs a, FinScratch w) {
+  __shared__ double red[kFinWaves * kFinSplit];
+  TURPY_LDS_INIT(red);
+  const uint32_t n = static_cast<uint32_t>(a.n);
+  const int64_t np = static_cast<int64_t>(n) * n;
+  double v[4] = {0, 0, 0, 0};
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kFinThreads + threadIdx.x; p < np;
+       p += static_cast<int64_t>(w.nb) * kFinThreads) {
+    const int i0 = static_cast<int>(static_cast<uint32_t>(p) / n), i1 = static_cast<int>(static_cast<uint32_t>(p) % n);
+    const double m1 = (static_cast<double>(a.moments[p]) - a.moments[np + p]) / a.count;
+    const double x = (i1 - a.n / 2) * a.dx, y = (i0 - a.n / 2) * a.dx;
+    v[0] += m1;
+    v[1] += (x * x + y * y) * m1;
+    v[2] += static_cast<float>(m1);
+    v[3] = fmax(v[3], m1);
+  }
+  finalize_join(v, w.first, w.nb, red, FinFirst());
+}
+
+// The bracket that pass q starts from: [lo, hi) of bit patterns with
+// S(lo) >= target, from pass q - 1's bracket and sums.  Same bits in every block.
+__device__ __forceinline__ void finalize_bracket(const FinalizeArgs& a, const FinScratch& w, int q, double* tot,
+                                                 uint32_t* lo, uint32_t* hi) {
+  __shared__ double first[4];
+  TURPY_LDS_INIT(first);
+  finalize_totals(w.first, w.nb, 4, first, FinFirst());
+  *lo = 0;
+  *hi = 0x7F800000u;  // +inf, above every finite m1
+  if (q == 0) return;
+  *lo = static_cast<uint32_t>(w.bracket[2 * (q - 1)]);
+  *hi = static_cast<uint32_t>(w.bracket[2 * (q - 1) + 1]);
+  const double target = a.power_fraction * first[2];
+  finalize_totals(w.split + static_cast<size_t>((q - 1) % 2) * kFinSplit * w.nb, w.nb, kFinSplit - 1, tot, FinAdd());
+  const uint32_t step = (*hi - *lo + kFinSplit - 1) / kFinSplit;
+  const uint32_t lo0 = *lo, hi0 = *hi;
+  for (int j = 1; j < kFinSplit; ++j) {
+    const uint32_t mid = lo0 + static_cast<uint32_t>(j) * step;
+    if (mid >= hi0) break;
+    if (tot[j - 1] >= target) {
+      *lo = mid;
+    } else {
+      *hi = mid;
+      break;
+    }
+  }
+}
+
+__global__ __launch_bounds__(kFinThreads) void finalize_bracket_kernel(FinalizeArgs a, FinScratch w, int q) {
+  __shared__ double red[kFinWaves * kFinSplit];
+  TURPY_LDS_INIT(red);
+  __shared__ double tot[kFinSplit];
+  TURPY_LDS_INIT(tot);
+  uint32_t lo, hi;
+  finalize_bracket(a, w, q, tot, &lo, &hi);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    w.bracket[2 * q] = lo;
+    w.bracket[2 * q + 1] = hi;
+  }
+  const int64_t np = static_cast<int64_t>(a.n) * a.n;
+  const uint32_t step = (hi - lo + kFinSplit - 1) / kFinSplit;
+  double v[kFinSplit - 1];
+#pragma unroll
+  for (int j = 0; j < kFinSplit - 1; ++j) v[j] = 0;
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kFinThreads + threadIdx.x; p < np;
+       p += static_cast<int64_t>(w.nb) * kFinThreads) {
+    const float m = mean_intensity(a, p, np);
+#pragma unroll
+    for (int j = 0; j < kFinSplit - 1; ++j)
+      if (m >= __uint_as_float(lo + static_cast<uint32_t>(j + 1) * step)) v[j] += m;
+  }
+  finalize_join(v, w.split + static_cast<size_t>(q % 2) * kFinSplit * w.nb, w.nb, red, FinAdd());
+}
+
+__global__ __launch_bounds__(kFinThreads) void finalize_region_kernel(FinalizeArgs a, FinScratch w) {
+  __shared__ double red[kFinWaves * kFinSplit];
+  TURPY_LDS_INIT(red);
+  __shared__ double tot[kFinSplit];
+  TURPY_LDS_INIT(tot);
+  __shared__ double first[4];
+  TURPY_LDS_INIT(first);
+  const uint32_t n = static_cast<uint32_t>(a.n);
+  const int64_t np = static_cast<int64_t>(n) * n;
+  uint32_t lo = 0, hi;
+  if (a.power_fraction > 0) {
+    finalize_bracket(a, w, kFinPasses, tot, &lo, &hi);
+    if (blockIdx.x == 0 && threadIdx.x == 0) w.bracket[2 * kFinPasses] = lo;
+  }
+  finalize_totals(w.first, w.nb, 4, first, FinFirst());
+  const float thr = __uint_as_float(lo);
+  const double cut = exp(-2.0) * first[3];
+  double v[7] = {0, 0, 0, 0, 0, 0, 0};
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kFinThreads + threadIdx.x; p < np;
+       p += static_cast<int64_t>(w.nb) * kFinThreads) {
+    const int i0 = static_cast<int>(static_cast<uint32_t>(p) / n), i1 = static_cast<int>(static_cast<uint32_t>(p) % n);
+    const double m1 = (static_cast<double>(a.moments[p]) - a.moments[np + p]) / a.count;
+    const bool in = a.power_fraction > 0 ? static_cast<float>(m1) >= thr
+                                         : abs(i0 - a.n / 2) < a.n / 4 && abs(i1 - a.n / 2) < a.n / 4;
+    if (in) {
+      const double m2 = (static_cast<double>(a.moments[2 * np + p]) - a.moments[3 * np + p]) / a.count;
+      const double wt = a.weight ? static_cast<double>(a.weight[p]) : 1.0;
+      v[0] += wt * (m2 / (m1 * m1) - 1.0);
+      v[1] += wt;
+    }
+    if (m1 >= cut && m1 > 0) {
+      const double x = (i1 - a.n / 2) * a.dx, y = (i0 - a.n / 2) * a.dx;
+      const double r2 = x * x + y * y, l = log(m1);
+      v[2] += 1;
+      v[3] += r2;
+      v[4] += r2 * r2;
+      v[5] += l;
+      v[6] += r2 * l;
+    }
+  }
+  finalize_join(v, w.region, w.nb, red, FinAdd());
+}
+
+__global__ __launch_bounds__(kFinThreads) void finalize_summary_kernel(FinalizeArgs a, FinScratch w) {
+  __shared__ double first[4], tot[7];
+  TURPY_LDS_INIT(first);
+  TURPY_LDS_INIT(tot);
+  finalize_totals(w.first, w.nb, 4, first, FinFirst());
+  finalize_totals(w.region, w.nb, 7, tot, FinAdd());
+  if (threadIdx.x != 0) return;
+  const float thr = a.power_fraction > 0 ? __uint_as_float(static_cast<uint32_t>(w.bracket[2 * kFinPasses])) : 0.0f;
+  finalize_write(a, first[0], first[1], tot[0], tot[1], thr, tot[2], tot[3], tot[4], tot[5], tot[6]);
+}
+
+__global__ __launch_bounds__(256) void finalize_map_kernel(FinalizeArgs a) {
+  const int64_t np = static_cast<int64_t>(a.n) * a.n;
+  const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+  if (p >= np) return;
+  const double m1 = (static_cast<double>(a.moments[p]) - a.moments[np + p]) / a.count;
+  const double m2 = (static_cast<double>(a.moments[2 * np + p]) - a.moments[3 * np + p]) / a.count;
+  a.si_map[p] = static_cast<float>(m2 / (m1 * m1) - 1.0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1631,8 +1861,25 @@ hipError_t launch_nonfinite(const float* x, int64_t count, unsigned long long* c
   return hipGetLastError();
 }
 
+// Many blocks where the SI map can hold their partial sums until it is
+// written (from n = 64 on it is larger than they are); one block without a
+// map, for a map off an 8-byte boundary, and on smaller grids.
 hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, s, a);
+  const int64_t np = static_cast<int64_t>(a.n) * a.n;
+  const int nb = finalize_blocks(np);
+  if (!a.si_map || reinterpret_cast<uintptr_t>(a.si_map) % sizeof(double) != 0 || a.n < 64 ||
+      finalize_scratch_bytes(nb) > np * static_cast<int64_t>(sizeof(float))) {
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(1024), 0, s, a);
+    return hipGetLastError();
+  }
+  const FinScratch w = finalize_scratch(reinterpret_cast<double*>(a.si_map), nb);
+  const dim3 grid(static_cast<uint32_t>(nb)), block(kFinThreads);
+  hipLaunchKernelGGL(finalize_sums_kernel, grid, block, 0, s, a, w);
+  if (a.power_fraction > 0)
+    for (int q = 0; q < kFinPasses; ++q) hipLaunchKernelGGL(finalize_bracket_kernel, grid, block, 0, s, a, w, q);
+  hipLaunchKernelGGL(finalize_region_kernel, grid, block, 0, s, a, w);
+  hipLaunchKernelGGL(finalize_summary_kernel, dim3(1), block, 0, s, a, w);
+  hipLaunchKernelGGL(finalize_map_kernel, dim3(static_cast<uint32_t>((np + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

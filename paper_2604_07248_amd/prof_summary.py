@@ -61,7 +61,7 @@ def family(kernel_name):
         return "row_fwd"
     for key, fam in (("row_moments_kernel", "row_moments"), ("col_pass", "col"), ("synth_", "synth"),
                      ("sh_kernel", "sh"), ("sh_group_kernel", "sh"), ("evolve_kernel", "evolve"),
-                     ("stats_kernel", "stats"), ("finalize_kernel", "finalize"), ("copy_kernel", "copy"),
+                     ("stats_kernel", "stats"), ("finalize_", "finalize"), ("copy_kernel", "copy"),
                      ("sum_planes_kernel", "sum"), ("noise_kernel", "noise"), ("nonfinite_kernel", "nonfinite"),
                      ("recv_row_in", "recv_row"), ("recv_col_grad", "recv_col_grad"), ("recv_col", "recv_col"),
                      ("recv_row_grad", "recv_row_grad"), ("recv_reduce", "recv_reduce")):
