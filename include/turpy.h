@@ -463,10 +463,10 @@ turpy_status turpy_place_screens(const turpy_cn2_profile* profile, double length
  *    N = 2048 K = 16 does not fit): K sets the block size, the occupancy and
  *    the width of each memory segment; results are bit-identical for every K;
  *  - the radix plan of their transforms: every transform starts with a
- *    radix-16 pass; the second pass has radix R2 (default min(16, N/16)) and
- *    the third N / (16 R2); R2 in {8, 4} is also built for N = 512 and 1024
- *    and R2 = 8 for N = 2048 (other plans round differently, within the
- *    oracle tolerance);
+ *    radix-16 pass; the second pass has radix R2 (default 8 from N = 512,
+ *    N/16 below) and the third N / (16 R2); R2 = 4 is also built for N = 512
+ *    and 1024, and R2 = 8 is accepted from N = 512 (other plans round
+ *    differently, within the oracle tolerance);
  *  - the occupancy hint of the screen row passes, forward and adjoint: the
  *    minimum waves per SIMD (2, 3 or 4) the register allocation must allow;
  *    3 is the default, 2 and 4 are built for N >= 256 (bit-identical results).

@@ -1210,8 +1210,8 @@ namespace {
 
 constexpr int kWidths[3] = {4, 8, 16};
 
-// Second-pass radices built per grid size for the column pass and the
-// synthesis (0 = the default plan, min(16, N/16)).
+// Second-pass radices accepted per grid size for the column pass and the
+// synthesis (0 = the default plan, which is radix 8 from N = 512).
 bool radix_built_rt(int n, int r) {
   return r == 0 || ((n == 512 || n == 1024) && (r == 8 || r == 4)) || (n == 2048 && r == 8);
 }
@@ -1421,7 +1421,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
   const int64_t plane = static_cast<int64_t>(n) * n;
   if (need_col) {
     ColArgs c = col_args(pl, 0, wsp.gbuf, plane, wsp.gbuf, pl->R, false);
-    if (turpy_status s = tune_key(ck, strip_choices(n), {default_col_width(n), 0, 0}, st, [&](const LaunchChoice& k) {
+    if (turpy_status s = tune_key(ck, strip_choices(n), {default_col_width(n, pl->R), 0, 0}, st, [&](const LaunchChoice& k) {
           c.width = k.width;
           c.radix = k.radix;
           return launch_col(n, c, st);
@@ -1431,7 +1431,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
   if (need_synth) {
     SynthArgs a = synth_args(pl, 0, 0, 0, nullptr, wsp);
     a.t_dev = nullptr;
-    if (turpy_status s = tune_key(sk, strip_choices(n), {default_synth_width(n), 0, 0}, st,
+    if (turpy_status s = tune_key(sk, strip_choices(n), {default_synth_width(n, pl->P), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
                                     a.width = k.width;
                                     a.radix = k.radix;
@@ -1450,7 +1450,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
     a.t_dev = nullptr;
     a.M = 1;
     bool flip = false;
-    if (turpy_status s = tune_key(ak, strip_choices(n), {default_synth_width(n), 0, 0}, st,
+    if (turpy_status s = tune_key(ak, strip_choices(n), {default_ar_width(n, pl->P), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
                                     a.width = k.width;
                                     a.radix = k.radix;
@@ -1503,8 +1503,8 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
 
 turpy_status turpy_plan_widths(const turpy_plan* pl, int32_t* col_width, int32_t* synth_width) {
   if (!pl) return fail(TURPY_E_INVALID, "plan_widths: NULL plan");
-  if (col_width) *col_width = pl->col_width ? pl->col_width : default_col_width(pl->n);
-  if (synth_width) *synth_width = pl->synth_width ? pl->synth_width : default_synth_width(pl->n);
+  if (col_width) *col_width = pl->col_width ? pl->col_width : default_col_width(pl->n, pl->R);
+  if (synth_width) *synth_width = pl->synth_width ? pl->synth_width : default_synth_width(pl->n, pl->P);
   return TURPY_OK;
 }
 
@@ -1520,13 +1520,13 @@ turpy_status turpy_plan_set_widths(turpy_plan* pl, int32_t col_width, int32_t sy
 
 turpy_status turpy_plan_config(const turpy_plan* pl, turpy_launch_config* out) {
   if (!pl || !out) return fail(TURPY_E_INVALID, "plan_config: NULL argument");
-  out->col_width = pl->col_width ? pl->col_width : default_col_width(pl->n);
+  out->col_width = pl->col_width ? pl->col_width : default_col_width(pl->n, pl->R);
   out->col_radix = pl->col_radix;
-  out->synth_width = pl->synth_width ? pl->synth_width : default_synth_width(pl->n);
+  out->synth_width = pl->synth_width ? pl->synth_width : default_synth_width(pl->n, pl->P);
   out->synth_radix = pl->synth_radix;
   out->row_waves = pl->row_waves ? pl->row_waves : 3;
   out->row_waves_bwd = pl->row_waves_bwd ? pl->row_waves_bwd : 3;
-  out->ar_width = pl->ar_width ? pl->ar_width : default_synth_width(pl->n);
+  out->ar_width = pl->ar_width ? pl->ar_width : default_ar_width(pl->n, pl->P);
   out->ar_radix = pl->ar_radix;
   return TURPY_OK;
 }

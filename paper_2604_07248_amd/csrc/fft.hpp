@@ -11,8 +11,8 @@
 // transform chain without an LDS round trip between them.
 //
 // Radix plan for E = 16: first pass radix 16 (no twiddles), second pass radix
-// R2 (default min(16, N/16)) at sub-length 16, third pass radix N/(16 R2) at
-// sub-length 16 R2.
+// R2 (default 8 from N = 512, else N/16) at sub-length 16, third pass radix
+// N/(16 R2) at sub-length 16 R2.
 #pragma once
 
 #include "device_common.hpp"
@@ -205,13 +205,17 @@ __device__ __forceinline__ void stockham_pass(float2 (&x)[E], const Lds& lds, in
 // Full length-N transform of the strided-layout registers (unnormalised in
 // both directions; forward uses exp(-2 pi i n k / N)).
 // WAVE: the T = N/E threads of the transform lie in one wavefront (see lds_sync).
-// R2SEL: radix of the second pass (0: min(16, N/16)); the third pass takes the
+// R2SEL: radix of the second pass (0: the default); the third pass takes the
 // rest, N / (16 R2SEL), at sub-length 16 R2SEL.  Every plan leaves its outputs
 // in the same strided natural-order layout (the last pass writes output index
 // j + (N/R) r back to slot q + (E/R) r, the slot it read).
+// The default from N = 512 is 8: two butterflies of 8 keep fewer values live
+// than one of 16 and the last pass gets a radix of 4 to 16 instead of 2 to 8
+// (column pass, 16 against 8, us: n = 512, R = 256 195 / 190; n = 1024, R = 32
+// 114.5 / 108.2; n = 2048, R = 8 155.7 / 150.9; the synthesis within 1 %).
 template <int N, int R2SEL>
 constexpr int second_radix() {
-  return R2SEL ? R2SEL : (N / 16 >= 16 ? 16 : N / 16);
+  return R2SEL ? R2SEL : (N >= 512 ? 8 : N / 16);
 }
 template <int N, int R2SEL>
 constexpr int fft_passes() {

@@ -1518,10 +1518,10 @@ hipError_t row_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
 }
 
 // Second-pass radices built for the column pass and the synthesis: the
-// default plan, and for N = 512..2048 the alternatives the tuner times.
-constexpr bool radix_built(int n, int r2) {
-  return r2 == 0 || ((n == 512 || n == 1024) && (r2 == 8 || r2 == 4)) || (n == 2048 && r2 == 8);
-}
+// default plan (radix 8 from N = 512, which asking for 8 selects too), and
+// for N = 512 and 1024 the alternative the tuner times.
+constexpr bool radix_built(int n, int r2) { return r2 == 0 || ((n == 512 || n == 1024) && r2 == 4); }
+constexpr int radix_plan(int n, int r2) { return n >= 512 && r2 == 8 ? 0 : r2; }
 
 template <int N, int K, int R2SEL>
 hipError_t col_launch_kr(const ColArgs& a, hipStream_t s) {
@@ -1542,19 +1542,18 @@ hipError_t col_launch_kr(const ColArgs& a, hipStream_t s) {
 
 template <int N, int K>
 hipError_t col_launch_k(const ColArgs& a, hipStream_t s) {
-  switch (a.radix) {
+  switch (radix_plan(N, a.radix)) {
     case 0: return col_launch_kr<N, K, 0>(a, s);
     case 4: return col_launch_kr<N, K, 4>(a, s);
-    case 8: return col_launch_kr<N, K, 8>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 // Strip width a.width (4, 8 or 16 columns per block), or the built-in choice
-// for N when a.width is 0; second-pass radix a.radix (0: the default plan).
+// for N and the planes when a.width is 0; second-pass radix a.radix (0: the default plan).
 template <int N>
 hipError_t col_launch(const ColArgs& a, hipStream_t s) {
-  switch (a.width ? a.width : col_width<N>()) {
+  switch (a.width ? a.width : default_col_width(N, a.R)) {
     case 4: return col_launch_k<N, 4>(a, s);
     case 8: return col_launch_k<N, 8>(a, s);
     case 16: return col_launch_k<N, 16>(a, s);
@@ -1576,17 +1575,16 @@ hipError_t synth_launch_kr(const SynthArgs& a, hipStream_t s) {
 
 template <int N, int K>
 hipError_t synth_launch_k(const SynthArgs& a, hipStream_t s) {
-  switch (a.radix) {
+  switch (radix_plan(N, a.radix)) {
     case 0: return synth_launch_kr<N, K, 0>(a, s);
     case 4: return synth_launch_kr<N, K, 4>(a, s);
-    case 8: return synth_launch_kr<N, K, 8>(a, s);
     default: return hipErrorInvalidValue;
   }
 }
 
 template <int N>
 hipError_t synth_launch(const SynthArgs& a, hipStream_t s) {
-  switch (a.width ? a.width : synth_width<N>()) {
+  switch (a.width ? a.width : (a.evolve ? default_ar_width(N, a.P) : default_synth_width(N, a.P))) {
     case 4: return synth_launch_k<N, 4>(a, s);
     case 8: return synth_launch_k<N, 8>(a, s);
     case 16: return synth_launch_k<N, 16>(a, s);
@@ -1757,10 +1755,9 @@ hipError_t col_group_launch_r(const ColArgs& proto, const ColArgs* tab, uint32_t
 template <int N>
 hipError_t col_group_launch(const ColArgs& proto, const ColArgs* tab, uint32_t count, const GroupCall& g,
                             hipStream_t s) {
-  switch (proto.radix) {
+  switch (radix_plan(N, proto.radix)) {
     case 0: return col_group_launch_r<N, 0>(proto, tab, count, g, s);
     case 4: return col_group_launch_r<N, 4>(proto, tab, count, g, s);
-    case 8: return col_group_launch_r<N, 8>(proto, tab, count, g, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -1781,10 +1778,9 @@ template <int N>
 hipError_t synth_group_launch(const SynthArgs& proto, const SynthArgs* tab, uint32_t count, const GroupCall& g,
                               hipStream_t s) {
   if (proto.spectra || proto.evolve) return hipErrorInvalidValue;  // synthesised screens only
-  switch (proto.radix) {
+  switch (radix_plan(N, proto.radix)) {
     case 0: return synth_group_launch_r<N, 0>(proto, tab, count, g, s);
     case 4: return synth_group_launch_r<N, 4>(proto, tab, count, g, s);
-    case 8: return synth_group_launch_r<N, 8>(proto, tab, count, g, s);
     default: return hipErrorInvalidValue;
   }
 }

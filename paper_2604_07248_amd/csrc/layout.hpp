@@ -15,18 +15,38 @@ constexpr int row_groups() {  // rows per block of the row kernels
 }
 template <int N>
 constexpr int row_block() { return row_groups<N>() * (N / kE); }
-// Columns per block of the column pass and of the screen synthesis, per grid
-// size, when no tuned choice is set: the fastest of 4, 8 and 16 measured on
-// MI355X at constant R N^2 (column pass: 16 up to N = 512, 8 above;
-// synthesis, whose VALU load per element is higher, 4 from N = 1024).
-constexpr int default_col_width(int n) { return n >= 1024 ? 8 : (n >= 256 ? 16 : 8); }
-constexpr int default_synth_width(int n) { return n >= 1024 ? 4 : default_col_width(n); }
+// Columns per block of the column pass, of the screen synthesis and of the
+// synthesis with the AR step fused into it, when no tuned choice is set.  The
+// widest strip that pays on a full chip (times at R N^2 = 2^26 pixels, us for
+// 4 / 8 / 16 columns, one launch bracketed by events):
+//   column pass  n = 128 27.7 / 21.7 / 16.4 (R = 256); 512: 263 / 201 / 190;
+//                1024: 268 / 220 / 277
+//   synthesis    n = 512 86.4 / 85.9 / 87.2; 1024: 85.8 / 89.5 / 118
+//   AR step      n = 512 226 / 180 / 151; 1024: 240 / 205 / 177 (a strip row of
+//                16 columns is a whole line, written back past the cache)
+// A launch over few planes takes narrower strips until it has a block for
+// every CU (n = 512, 4 planes: 16 columns 15.4 us, 8 columns 13.7; n = 1024,
+// one plane of the AR step: 23.0 us for 16 columns, 15.9 for 4), as long as
+// a block keeps a whole wave.
+constexpr int kFillBlocks = 256;
+constexpr int fill_width(int n, int64_t planes, int widest) {
+  int k = widest;
+  while (k > 4 && (n / k) * planes < kFillBlocks && (k / 2) * (n / kE) >= 64) k /= 2;
+  return k;
+}
+constexpr int widest_col(int n) { return n >= 1024 ? 8 : (n >= 128 ? 16 : 8); }
+constexpr int widest_synth(int n) { return n >= 1024 ? 4 : (n >= 512 ? 8 : widest_col(n)); }
+constexpr int widest_ar(int n) { return n >= 2048 ? 8 : (n >= 128 ? 16 : 8); }
+constexpr int default_col_width(int n, int64_t planes) { return fill_width(n, planes, widest_col(n)); }
+constexpr int default_synth_width(int n, int64_t planes) { return fill_width(n, planes, widest_synth(n)); }
+constexpr int default_ar_width(int n, int64_t planes) { return fill_width(n, planes, widest_ar(n)); }
+// Grouped launches and the receiver, whose members together fill the chip.
 template <int N>
-constexpr int col_width() { return default_col_width(N); }
+constexpr int col_width() { return widest_col(N); }
 template <int N>
 constexpr int col_block() { return col_width<N>() * (N / kE); }
 template <int N>
-constexpr int synth_width() { return default_synth_width(N); }
+constexpr int synth_width() { return widest_synth(N); }
 
 // A strip of K columns is built for grid size N when its block (K N / 16
 // threads) stays within 1024 threads and its LDS (K N complex words beside
