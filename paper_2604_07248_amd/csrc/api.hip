@@ -291,7 +291,6 @@ void keep_screens(const turpy_plan* pl, void* checkpoints, int32_t src, Ws* w) {
   if (!pl->screen_ck || !checkpoints || src == TURPY_SCREENS_MATERIALIZED || pl->M == 0) return;
   const size_t plane = static_cast<size_t>(pl->n) * pl->n;
   w->screens = static_cast<float2*>(checkpoints) + static_cast<size_t>(pl->R) * pl->M * plane;
-  w->screen_stride = static_cast<size_t>(pl->P) * plane;
 }
 
 turpy_status check_t(int64_t t) {
@@ -299,21 +298,24 @@ turpy_status check_t(int64_t t) {
   return TURPY_OK;
 }
 
+// The column halves of screen s, and of the screens that share its launch,
+// unless the last such launch (`*ready`, a batch index, -1 at the start)
+// already covered it.
 hipError_t enqueue_screen_col(const turpy_plan* pl, uint64_t seed, uint32_t t, int s, const float2* spectra,
-                              const Ws& w, hipStream_t st, const EvolveStep* ev = nullptr) {
-  const SynthArgs a = synth_args(pl, seed, t, s, spectra, w, ev);
+                              const Ws& w, int* ready, hipStream_t st, const EvolveStep* ev = nullptr) {
+  const int q = s / w.batch;
+  if (*ready == q) return hipSuccess;
+  *ready = q;
+  const int first = q * w.batch, count = std::min(w.batch, pl->M - first);
+  const SynthArgs a = synth_args(pl, seed, t, first, count, spectra, w, ev);
   return timed("synth", st, [&] { return launch_synth(pl->n, a, st); });
 }
 
-// Column pass of distance `step` over all realizations; with synth_screen >= 0
-// the column half of that screen's synthesis follows it into ws.scratch.
+// Column pass of distance `step` over all realizations.
 hipError_t enqueue_col(const turpy_plan* pl, int step, const float2* in, int64_t in_stride, float2* out,
-                       bool adjoint, int synth_screen, uint64_t seed, uint32_t t, const float2* spectra,
-                       const Ws& w, hipStream_t st, const EvolveStep* ev = nullptr) {
+                       bool adjoint, hipStream_t st) {
   const ColArgs c = col_args(pl, step, in, in_stride, out, pl->R, adjoint);
-  TURPY_HIP_E(timed("col", st, [&] { return launch_col(pl->n, c, st); }));
-  if (synth_screen >= 0) return enqueue_screen_col(pl, seed, t, synth_screen, spectra, w, st, ev);
-  return hipSuccess;
+  return timed("col", st, [&] { return launch_col(pl->n, c, st); });
 }
 
 // Fresh subharmonic coefficients of every pair and screen (revolutions) into ws.sh.
@@ -447,8 +449,9 @@ turpy_status turpy_screen_generate(turpy_plan* pl, uint64_t seed, int64_t t, flo
   if (turpy_status s_ = check_capture(pl, st, "screen_generate")) return s_;
   const Ws w = carve(pl, ws);
   if (pl->sh_levels > 0) TURPY_HIP(enqueue_sh(pl, seed, static_cast<uint32_t>(t), w, st), "screen_generate: sh");
+  int ready = -1;
   for (int s = 0; s < pl->M; ++s) {
-    TURPY_HIP(enqueue_screen_col(pl, seed, static_cast<uint32_t>(t), s, nullptr, w, st), "screen_generate: col");
+    TURPY_HIP(enqueue_screen_col(pl, seed, static_cast<uint32_t>(t), s, nullptr, w, &ready, st), "screen_generate: col");
     RowArgs a = base_row(pl);
     screen_fields(pl, TURPY_SCREENS_SYNTH, nullptr, w, s, &a);
     a.screen_mode = ROW_SCRATCH;
@@ -498,7 +501,7 @@ turpy_status propagate_impl(turpy_plan* pl, uint64_t seed, int64_t t, const void
   bool spectral = false;
   const bool synth = src != TURPY_SCREENS_MATERIALIZED;
   const uint32_t tt = static_cast<uint32_t>(t);
-  bool scratch_ready = false;  // the scratch plane holds the next row pass's screen
+  int ready = -1;  // the batch of screens now in the scratch
   if (pl->dz[0] > 0) {
     // row transform of the source (x h_0(k1)), then the first column pass
     RowArgs a = base_row(pl);
@@ -525,18 +528,15 @@ turpy_status propagate_impl(turpy_plan* pl, uint64_t seed, int64_t t, const void
       cur = w.src;
       cur_stride = 0;
     } else {
-      const int syn = synth && M > 0 ? 0 : -1;
-      TURPY_HIP(enqueue_col(pl, 0, dst, plane, uout, false, syn, seed, tt, spectra, w, st, ev),
-                "propagate: column pass 0");
-      scratch_ready = syn >= 0;
+      TURPY_HIP(enqueue_col(pl, 0, dst, plane, uout, false, st), "propagate: column pass 0");
       cur = uout;
       cur_stride = plane;
     }
     spectral = true;
   }
   for (int s = 0; s < M; ++s) {
-    if (synth && !scratch_ready)
-      TURPY_HIP(enqueue_screen_col(pl, seed, tt, s, spectra, w, st, ev), "propagate: screen col");
+    if (synth)
+      TURPY_HIP(enqueue_screen_col(pl, seed, tt, s, spectra, w, &ready, st, ev), "propagate: screen col");
     const bool out_spec = pl->dz[s + 1] > 0;
     RowArgs a = base_row(pl);
     a.in = cur;
@@ -552,13 +552,8 @@ turpy_status propagate_impl(turpy_plan* pl, uint64_t seed, int64_t t, const void
     cur = uout;
     cur_stride = plane;
     spectral = out_spec;
-    scratch_ready = false;
-    if (out_spec) {
-      const int syn = synth && s + 1 < M ? s + 1 : -1;
-      TURPY_HIP(enqueue_col(pl, s + 1, uout, plane, uout, false, syn, seed, tt, spectra, w, st, ev),
-                "propagate: column pass");
-      scratch_ready = syn >= 0;
-    }
+    if (out_spec)
+      TURPY_HIP(enqueue_col(pl, s + 1, uout, plane, uout, false, st), "propagate: column pass");
   }
   if (spectral) {
     RowArgs a = base_row(pl);
@@ -705,7 +700,7 @@ static turpy_status backward_checkpointed(turpy_plan* pl, uint64_t seed, int64_t
   bool spectral = false;
   const bool synth = src != TURPY_SCREENS_MATERIALIZED && !stored;
   const uint32_t tt = static_cast<uint32_t>(t);
-  bool scratch_ready = false;
+  int ready = -1;  // the batch of screens now in the scratch
   if (pl->dz[M] > 0) {
     RowArgs a = base_row(pl);  // adjoint of the final (1/N) inverse row transform
     a.in = gout;
@@ -715,16 +710,13 @@ static turpy_status backward_checkpointed(turpy_plan* pl, uint64_t seed, int64_t
     a.scale = inv_n;
     TURPY_HIP(timed(row_family(a), st, [&] { return launch_row(n, a, pl->P, st); }),
               "propagate_backward: first row pass");
-    const int syn = synth && M > 0 ? M - 1 : -1;
-    TURPY_HIP(enqueue_col(pl, M, g, plane, g, true, syn, seed, tt, spectra, w, st),
-              "propagate_backward: column pass");
-    scratch_ready = syn >= 0;
+    TURPY_HIP(enqueue_col(pl, M, g, plane, g, true, st), "propagate_backward: column pass");
     cur = g;
     spectral = true;
   }
   for (int s = M - 1; s >= 0; --s) {
-    if (synth && !scratch_ready)
-      TURPY_HIP(enqueue_screen_col(pl, seed, tt, s, spectra, w, st), "propagate_backward: screen col");
+    if (synth)
+      TURPY_HIP(enqueue_screen_col(pl, seed, tt, s, spectra, w, &ready, st), "propagate_backward: screen col");
     const bool out_spec = pl->dz[s] > 0;
     RowArgs a = base_row(pl);
     a.in = cur;
@@ -744,19 +736,13 @@ static turpy_status backward_checkpointed(turpy_plan* pl, uint64_t seed, int64_t
               "propagate_backward: row pass");
     cur = g;
     spectral = out_spec;
-    scratch_ready = false;
     if (s == 0 && shared) {
       float2* dst = spectral ? w.src : static_cast<float2*>(grad_u_in);
       TURPY_HIP(timed("sum", st, [&] { return launch_sum_planes(g, pl->R, plane, dst, st); }),
                 "propagate_backward: sum over realizations");
       return adjoint_shared_tail(pl, w.src, spectral, static_cast<float2*>(grad_u_in), st);
     }
-    if (out_spec) {
-      const int syn = synth && s > 0 ? s - 1 : -1;
-      TURPY_HIP(enqueue_col(pl, s, g, plane, g, true, syn, seed, tt, spectra, w, st),
-                "propagate_backward: column pass");
-      scratch_ready = syn >= 0;
-    }
+    if (out_spec) TURPY_HIP(enqueue_col(pl, s, g, plane, g, true, st), "propagate_backward: column pass");
   }
   if (spectral) {
     RowArgs a = base_row(pl);  // adjoint of the source row transform: conj h_0, unnormalised inverse
@@ -830,15 +816,16 @@ static turpy_status backward_reversible(turpy_plan* pl, uint64_t seed, int64_t t
       a.scale = inv_n;
       TURPY_HIP(timed(row_family(a), st, [&] { return launch_row(n, a, pl->P, st); }),
                 "propagate_backward_reversible: first row pass");
-      TURPY_HIP(enqueue_col(pl, M, a.out, plane, a.out, true, -1, seed, tt, spectra, w, st),
-                "propagate_backward_reversible: column pass");
+      TURPY_HIP(enqueue_col(pl, M, a.out, plane, a.out, true, st), "propagate_backward_reversible: column pass");
     }
     gc = g;
     uc = ub;
     spectral = true;
   }
+  int ready = -1;  // the batch of screens now in the scratch
   for (int s = M - 1; s >= 0; --s) {
-    if (synth) TURPY_HIP(enqueue_screen_col(pl, seed, tt, s, spectra, w, st), "propagate_backward_reversible: screen");
+    if (synth)
+      TURPY_HIP(enqueue_screen_col(pl, seed, tt, s, spectra, w, &ready, st), "propagate_backward_reversible: screen");
     const bool out_spec = pl->dz[s] > 0;
     for (int chain = 1; chain >= 0; --chain) {  // the field first, then the gradient that reads it
       RowArgs a = base_row(pl);
@@ -855,7 +842,6 @@ static turpy_status backward_reversible(turpy_plan* pl, uint64_t seed, int64_t t
       screen_fields(pl, src, screens_or_spectra, w, s, &a);
       a.backward = 1;
       a.waves = pl->row_waves_bwd;
-    a.waves = pl->row_waves_bwd;
       a.ckpt_single = 1;
       if (chain == 1) {
         a.ckpt_out = wb;
@@ -872,8 +858,7 @@ static turpy_status backward_reversible(turpy_plan* pl, uint64_t seed, int64_t t
         return adjoint_shared_tail(pl, w.src, out_spec, static_cast<float2*>(grad_u_in), st);
       }
       if (cont)
-        TURPY_HIP(enqueue_col(pl, s, a.out, plane, a.out, true, -1, seed, tt, spectra, w, st),
-                  "propagate_backward_reversible: column pass");
+        TURPY_HIP(enqueue_col(pl, s, a.out, plane, a.out, true, st), "propagate_backward_reversible: column pass");
     }
     gc = g;
     uc = ub;
@@ -1429,7 +1414,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
       return s;
   }
   if (need_synth) {
-    SynthArgs a = synth_args(pl, 0, 0, 0, nullptr, wsp);
+    SynthArgs a = synth_args(pl, 0, 0, 0, 1, nullptr, wsp);
     a.t_dev = nullptr;
     if (turpy_status s = tune_key(sk, strip_choices(n), {default_synth_width(n, pl->P), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
@@ -1446,7 +1431,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
     // reads is not the one the launch before it left in the last-level cache
     const EvolveStep ev{0.99, 0.5, 0.25};
     float2* second = reinterpret_cast<float2*>(static_cast<char*>(ws) + pl->off_ubuf());
-    SynthArgs a = synth_args(pl, 0, 1, 0, wsp.gbuf, wsp, &ev);
+    SynthArgs a = synth_args(pl, 0, 1, 0, 1, wsp.gbuf, wsp, &ev);
     a.t_dev = nullptr;
     a.M = 1;
     bool flip = false;

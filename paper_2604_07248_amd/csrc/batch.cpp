@@ -34,9 +34,7 @@ std::atomic<size_t> g_group_limit{kDefaultGroupLimit};
 // Bytes a member keeps in flight during a group's pass: its fields and its
 // workspace slice.
 size_t member_bytes(const turpy_plan* pl, const turpy_path& p) {
-  size_t ws = 0;
-  turpy_workspace_size(pl, TURPY_OP_PROPAGATE, &ws);
-  return static_cast<size_t>(p.realizations) * p.n * p.n * 8 + ws;
+  return static_cast<size_t>(p.realizations) * p.n * p.n * 8 + turpy::group_member_workspace(pl);
 }
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }

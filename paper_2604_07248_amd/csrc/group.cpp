@@ -74,6 +74,10 @@ std::string group_key(const turpy_plan* pl) {
   return std::to_string(pl->n) + "/" + std::to_string(pl->R) + "/" + std::to_string(mode);
 }
 
+size_t group_member_workspace(const turpy_plan* pl) {
+  return align_up(static_cast<size_t>(pl->P) * pl->plane_bytes()) + pl->off_src() - pl->off_sh();
+}
+
 size_t group_workspace(const Group* g) { return g->ws_bytes; }
 
 int64_t group_cost(const Group* g) {
@@ -110,7 +114,7 @@ turpy_status group_create(std::vector<GroupMember> members, Group** out) {
   g->device = p0->device;
   for (const GroupMember& m : members) {
     g->ws_off.push_back(g->ws_bytes);
-    g->ws_bytes += align_up(m.plan->ws_forward());
+    g->ws_bytes += align_up(group_member_workspace(m.plan));
     g->has_sh = g->has_sh || m.plan->sh_levels > 0;
   }
   const size_t cnt = members.size();
@@ -136,8 +140,9 @@ turpy_status group_create(std::vector<GroupMember> members, Group** out) {
   auto ws_of = [&](size_t k) {
     const turpy_plan* pl = members[k].plan;
     const size_t b = g->ws_off[k];
-    Ws w{off_ptr<float2>(b), off_ptr<float2>(b + pl->off_sh()), off_ptr<float2>(b + pl->off_src()),
-         off_ptr<float2>(b + pl->off_gbuf())};
+    Ws w{};
+    w.scratch = off_ptr<float2>(b);
+    w.sh = off_ptr<float2>(b + align_up(static_cast<size_t>(pl->P) * pl->plane_bytes()));
     return w;
   };
   auto field = [&](size_t k) { return off_ptr<float2>(members[k].field_bytes); };
@@ -169,7 +174,7 @@ turpy_status group_create(std::vector<GroupMember> members, Group** out) {
   };
   auto synth = [&](uint32_t count, auto&& screen) {
     add(K_SYNTH, count, [&](size_t k) {
-      return synth_args(members[k].plan, members[k].seed_offset, 0, screen(k), nullptr, ws_of(k));
+      return synth_args(members[k].plan, members[k].seed_offset, 0, screen(k), 1, nullptr, ws_of(k));
     });
   };
   auto M_of = [&](size_t k) { return members[k].plan->M; };

@@ -35,6 +35,9 @@ struct GroupMember {
 // Builds the schedule and uploads its argument records (synchronous).
 turpy_status group_create(std::vector<GroupMember> members, Group** out);
 void group_destroy(Group* g);
+// Workspace slice of a member: the scratch of one screen (the members together
+// fill a launch) and its subharmonic coefficients.
+size_t group_member_workspace(const turpy_plan* pl);
 size_t group_workspace(const Group* g);
 int64_t group_cost(const Group* g);
 // The forward pass of every member, as turpy_propagate with synthesised

@@ -681,10 +681,15 @@ void col_pass_kernel(ColArgs a) { col_pass_body<N, ANGULAR, K, R2SEL>(a); }
 
 // ---------------------------------------------------------------------------
 // Column half of the screen synthesis: noise x PSD weight (Eq. S16/S17), or a
-// stored spectrum, then the unnormalised inverse transform along y.
+// stored spectrum, then the unnormalised inverse transform along y.  A launch
+// covers `count` consecutive screens (the y index of its grid): screens do not
+// depend on each other or on the field, and where all pairs' planes of one
+// screen are far from filling the chip a launch per screen costs its 5 us
+// whatever it does (ten screens of one 256 x 256 realization: 55 us in ten
+// launches, 8 us in one).
 // ---------------------------------------------------------------------------
 template <int N, int K, int R2SEL>
-__device__ __forceinline__ void synth_col_body(const SynthArgs& a) {
+__device__ __forceinline__ void synth_col_body(const SynthArgs& a, int slot) {
   constexpr int T = N / kE;
   constexpr int STRIPS = N / K;
   __shared__ float2 smem[ColLds<K>::words(N)];
@@ -699,12 +704,14 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a) {
   __shared__ float2 tw_lds[N];
   const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
   float2 x[kE];
+  const uint32_t screen = a.screen + static_cast<uint32_t>(slot);
+  const float amp = a.amp[slot];
   if (a.evolve) {
     // Eq. 4 (translation by exp(-2 pi i (kx sx + ky sy)/N), the phase reduced
     // in FP64) then Eq. 5 (alpha blend with fresh innovations), bin pairs
     // (k0, k1), (k0 + N/2, k1) sharing one Philox block; DC kept at zero
     constexpr float inv2pi = 0.15915494309189535f;
-    float2* st = a.state + (static_cast<size_t>(j) * a.M + a.screen) * N * N + k1 + static_cast<size_t>(t) * N;
+    float2* st = a.state + (static_cast<size_t>(j) * a.M + screen) * N * N + k1 + static_cast<size_t>(t) * N;
     const int kx = signed_bin(k1, N);
     const double inv_n = 1.0 / N;
     float2 old[kE];
@@ -714,13 +721,13 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a) {
     for (int m = 0; m < kE / 2; ++m) {
       const int k0 = t + T * m;  // < N/2
       const uint32_t e = static_cast<uint32_t>(k0) * N + k1;
-      const uint4 v = philox4x32_10(noise_counter(e, time_step(a), static_cast<uint32_t>(j), a.ar_tag, a.screen),
+      const uint4 v = philox4x32_10(noise_counter(e, time_step(a), static_cast<uint32_t>(j), a.ar_tag, screen),
                                     a.key0, a.key1);
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const int kk0 = k0 + h * (N / 2);
         const int ky = signed_bin(kk0, N);
-        const float w = psd_amp(ky * ky + kx * kx, a.amp_rad, a.df2, a.inner, a.f02, a.q);
+        const float w = psd_amp(ky * ky + kx * kx, amp, a.df2, a.inner, a.f02, a.q);
         const float2 nc = h == 0 ? box_muller(v.x, v.y) : box_muller(v.z, v.w);
         double rev = -(static_cast<double>(kx) * a.sx + static_cast<double>(ky) * a.sy) * inv_n;
         rev -= rint(rev);
@@ -741,7 +748,7 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a) {
     }
   } else if (a.spectra) {
     constexpr float inv2pi = 0.15915494309189535f;
-    const float2* src = a.spectra + (static_cast<size_t>(j) * a.M + a.screen) * N * N + k1;
+    const float2* src = a.spectra + (static_cast<size_t>(j) * a.M + screen) * N * N + k1;
 #pragma unroll
     for (int m = 0; m < kE; ++m)
       x[m] = c_scale((src + static_cast<size_t>(t) * N)[static_cast<size_t>(T * m) * N], inv2pi);
@@ -751,25 +758,25 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a) {
     for (int m = 0; m < kE / 2; ++m) {
       const int k0 = t + T * m;  // < N/2
       const uint32_t e = static_cast<uint32_t>(k0) * N + k1;
-      const uint4 v = philox4x32_10(noise_counter(e, time_step(a), static_cast<uint32_t>(j), a.tag, a.screen), a.key0,
+      const uint4 v = philox4x32_10(noise_counter(e, time_step(a), static_cast<uint32_t>(j), a.tag, screen), a.key0,
                                     a.key1);
       const int ky_lo = k0;             // signed bin of k0 (< N/2)
       const int ky_hi = k0 - N / 2;     // signed bin of k0 + N/2
-      const float w_lo = psd_amp(ky_lo * ky_lo + kx * kx, a.amp, a.df2, a.inner, a.f02, a.q);
-      const float w_hi = psd_amp(ky_hi * ky_hi + kx * kx, a.amp, a.df2, a.inner, a.f02, a.q);
+      const float w_lo = psd_amp(ky_lo * ky_lo + kx * kx, amp, a.df2, a.inner, a.f02, a.q);
+      const float w_hi = psd_amp(ky_hi * ky_hi + kx * kx, amp, a.df2, a.inner, a.f02, a.q);
       x[m] = c_scale(box_muller(v.x, v.y), w_lo);
       x[m + kE / 2] = c_scale(box_muller(v.z, v.w), w_hi);
     }
   }
   fft<N, kE, true, false, R2SEL>(x, lds, t, tw);
-  float2* dst = a.scratch + j * static_cast<int64_t>(N) * N + k1;
+  float2* dst = a.scratch + slot * a.screen_stride + j * static_cast<int64_t>(N) * N + k1;
 #pragma unroll
   for (int m = 0; m < kE; ++m) (dst + static_cast<size_t>(t) * N)[static_cast<size_t>(T * m) * N] = x[m];
 }
 
 template <int N, int K, int R2SEL>
 __global__ __launch_bounds__(K * (N / kE))
-void synth_col_kernel(SynthArgs a) { synth_col_body<N, K, R2SEL>(a); }
+void synth_col_kernel(SynthArgs a) { synth_col_body<N, K, R2SEL>(a, blockIdx.y); }
 
 // ---------------------------------------------------------------------------
 // Subharmonic coefficients of Eq. 2 for every (pair, screen), and their mean.
@@ -1567,8 +1574,8 @@ hipError_t synth_launch_kr(const SynthArgs& a, hipStream_t s) {
     return hipErrorInvalidValue;
   } else {
     const uint64_t blocks = static_cast<uint64_t>(N / K) * a.P;
-    hipLaunchKernelGGL((synth_col_kernel<N, K, R2SEL>), dim3(static_cast<uint32_t>(blocks)), dim3(K * (N / kE)), 0, s,
-                       a);
+    hipLaunchKernelGGL((synth_col_kernel<N, K, R2SEL>), dim3(static_cast<uint32_t>(blocks), a.count),
+                       dim3(K * (N / kE)), 0, s, a);
     return hipGetLastError();
   }
 }
@@ -1584,7 +1591,7 @@ hipError_t synth_launch_k(const SynthArgs& a, hipStream_t s) {
 
 template <int N>
 hipError_t synth_launch(const SynthArgs& a, hipStream_t s) {
-  switch (a.width ? a.width : (a.evolve ? default_ar_width(N, a.P) : default_synth_width(N, a.P))) {
+  switch (a.width ? a.width : (a.evolve ? default_ar_width(N, a.P * a.count) : default_synth_width(N, a.P * a.count))) {
     case 4: return synth_launch_k<N, 4>(a, s);
     case 8: return synth_launch_k<N, 8>(a, s);
     case 16: return synth_launch_k<N, 16>(a, s);
@@ -1681,7 +1688,7 @@ __global__ __launch_bounds__(synth_width<N>() * (N / kE)) void synth_group_kerne
   group_key(g, &a.key0, &a.key1);
   a.t = g.t;
   a.t_dev = g.t_dev;
-  synth_col_body<N, synth_width<N>(), R2SEL>(a);
+  synth_col_body<N, synth_width<N>(), R2SEL>(a, 0);
 }
 
 __global__ __launch_bounds__(64) void sh_group_kernel(const ShArgs* tab, GroupCall g) {

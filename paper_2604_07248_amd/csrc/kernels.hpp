@@ -62,16 +62,24 @@ struct ColArgs {
   int radix;                // radix of the transforms' second pass (0: the default plan)
 };
 
+// Screens one synthesis launch can cover (their amplitudes travel in its
+// arguments).
+constexpr int kSynthScreens = 24;
+
 struct SynthArgs {
   const float2* tw;
-  float2* scratch;          // [P][N][N]
+  float2* scratch;          // [P][N][N] of the launch's first screen
+  size_t screen_stride;     // elements from one screen's planes to the next's
+  int count;                // screens of the launch
   int64_t P;                // realization pairs
   uint32_t key0, key1;      // Philox key (seed)
   uint32_t t;               // time step
   const uint32_t* t_dev;    // or, when set, read here at run time
-  uint32_t screen;
+  uint32_t screen;          // the first one
   uint32_t tag;
-  float amp;                // sqrt(0.023) r0^(-5/6) df / (2 pi): revolutions
+  // sqrt(0.023) r0^(-5/6) df of each screen: over 2 pi (revolutions), or in
+  // radians with the AR step
+  float amp[kSynthScreens];
   float df2;                // df^2
   float inner;              // log2(e) / (2 fm^2), 0 when no inner-scale cutoff
   float f02;                // f0^2
@@ -89,7 +97,6 @@ struct SynthArgs {
   uint32_t ar_tag;          // innovation tag
   float alpha_f, blend;     // alpha and sqrt(1 - alpha^2), rounded from FP64
   double sx, sy;            // frozen-flow shift in pixels
-  float amp_rad;            // sqrt(0.023) r0^(-5/6) df of this screen: radians
 };
 
 struct ShArgs {

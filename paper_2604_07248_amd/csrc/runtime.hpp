@@ -7,6 +7,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cmath>
 #include <cstdint>
@@ -45,6 +46,10 @@ turpy_status hip_fail(hipError_t e, const char* where);
 constexpr double kPi = 3.14159265358979323846;
 constexpr double kLog2e = 1.4426950408889634;
 constexpr size_t kAlign = 256;
+// Screens whose column halves together take no more than this are synthesised
+// in one launch.  A launch over 32 MiB of planes fills the chip (512 strips of
+// 1024 x 4 a plane pair), so larger batches would only hold more memory.
+constexpr size_t kBatchScratch = size_t(32) << 20;
 
 inline size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 inline bool pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
@@ -144,7 +149,13 @@ struct turpy_plan {
   std::string arch;              // device architecture (tuning-cache key)
 
   size_t plane_bytes() const { return static_cast<size_t>(n) * n * sizeof(float2); }
-  size_t off_sh() const { return turpy::align_up(static_cast<size_t>(P) * plane_bytes()); }
+  // scratch: the column halves of as many screens as fit kBatchScratch, at least one
+  size_t scratch_bytes() const {
+    const size_t one = static_cast<size_t>(P) * plane_bytes();
+    const size_t all = one * static_cast<size_t>(M > 0 ? M : 1);
+    return std::max(one, std::min(all, turpy::kBatchScratch / one * one));
+  }
+  size_t off_sh() const { return turpy::align_up(scratch_bytes()); }
   size_t off_src() const {
     return off_sh() + turpy::align_up(sh_levels > 0 ? static_cast<size_t>(P) * (M > 0 ? M : 1) * 32 * sizeof(float2) : 0);
   }
@@ -169,14 +180,24 @@ struct Ws {
   // column halves of the screens kept with the checkpoints (plans created with
   // TURPY_SCREEN_CHECKPOINTS): [M][P][N][N], or NULL to use `scratch`
   float2* screens = nullptr;
-  size_t screen_stride = 0;
-  float2* screen(int s) const { return screens ? screens + static_cast<size_t>(s) * screen_stride : scratch; }
+  size_t screen_stride = 0;  // elements between the planes of consecutive screens
+  // screens synthesised by one launch: those with the same s / batch, screen s
+  // in slot s % batch of the scratch
+  int batch = 1;
+  float2* screen(int s) const {
+    return screens ? screens + static_cast<size_t>(s) * screen_stride
+                   : scratch + static_cast<size_t>(s % batch) * screen_stride;
+  }
 };
 
 inline Ws carve(const turpy_plan* pl, void* ws) {
   char* b = static_cast<char*>(ws);
-  return Ws{reinterpret_cast<float2*>(b), reinterpret_cast<float2*>(b + pl->off_sh()),
-            reinterpret_cast<float2*>(b + pl->off_src()), reinterpret_cast<float2*>(b + pl->off_gbuf())};
+  Ws w{reinterpret_cast<float2*>(b), reinterpret_cast<float2*>(b + pl->off_sh()),
+       reinterpret_cast<float2*>(b + pl->off_src()), reinterpret_cast<float2*>(b + pl->off_gbuf())};
+  w.screen_stride = static_cast<size_t>(pl->P) * pl->n * pl->n;
+  w.batch = std::max(1, std::min({pl->M, kSynthScreens,
+                                  static_cast<int>(pl->scratch_bytes() / (w.screen_stride * sizeof(float2)))}));
+  return w;
 }
 
 inline void key_of(uint64_t seed, uint32_t* k0, uint32_t* k1) {
@@ -230,18 +251,21 @@ struct EvolveStep {
   double alpha, sx, sy;
 };
 
-inline SynthArgs synth_args(const turpy_plan* pl, uint64_t seed, uint32_t t, int s, const float2* spectra, const Ws& w,
-                     const EvolveStep* ev = nullptr) {
+// Synthesis of screens s .. s + count - 1 into their places in the workspace.
+inline SynthArgs synth_args(const turpy_plan* pl, uint64_t seed, uint32_t t, int s, int count, const float2* spectra,
+                            const Ws& w, const EvolveStep* ev = nullptr) {
   SynthArgs a{};
   a.tw = pl->d_tw;
   a.scratch = w.screen(s);
+  a.screen_stride = w.screen_stride;
+  a.count = count;
   a.P = pl->P;
   key_of(seed, &a.key0, &a.key1);
   a.t = t;
   a.t_dev = pl->d_t;
   a.screen = static_cast<uint32_t>(s);
   a.tag = TAG_MAIN;
-  a.amp = pl->amp_rev[s];
+  for (int i = 0; i < count; ++i) a.amp[i] = ev ? pl->amp_rad[s + i] : pl->amp_rev[s + i];
   a.df2 = pl->df2;
   a.inner = pl->inner;
   a.f02 = pl->f02;
@@ -258,7 +282,6 @@ inline SynthArgs synth_args(const turpy_plan* pl, uint64_t seed, uint32_t t, int
     a.blend = static_cast<float>(std::sqrt(1.0 - ev->alpha * ev->alpha));
     a.sx = ev->sx;
     a.sy = ev->sy;
-    a.amp_rad = pl->amp_rad[s];
   }
   return a;
 }
