@@ -291,6 +291,10 @@ void keep_screens(const turpy_plan* pl, void* checkpoints, int32_t src, Ws* w) {
   if (!pl->screen_ck || !checkpoints || src == TURPY_SCREENS_MATERIALIZED || pl->M == 0) return;
   const size_t plane = static_cast<size_t>(pl->n) * pl->n;
   w->screens = static_cast<float2*>(checkpoints) + static_cast<size_t>(pl->R) * pl->M * plane;
+  w->screen_stride = static_cast<size_t>(pl->P) * plane;
+  w->batch = std::max(1, std::min({pl->M, kSynthScreens,
+                                   static_cast<int>(pl->scratch_bytes() / (w->screen_stride * sizeof(float2)))}));
+  w->solo = false;  // full planes, as the buffer's layout says
 }
 
 turpy_status check_t(int64_t t) {
@@ -447,7 +451,8 @@ turpy_status turpy_screen_generate(turpy_plan* pl, uint64_t seed, int64_t t, flo
     return fail(TURPY_E_WORKSPACE, "screen_generate: workspace %zu < %zu bytes", ws_bytes, pl->ws_forward());
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (turpy_status s_ = check_capture(pl, st, "screen_generate")) return s_;
-  const Ws w = carve(pl, ws);
+  // the output is every row of the complex screens: full scratch planes
+  const Ws w = carve(pl, ws, TURPY_SCREENS_SPECTRA);
   if (pl->sh_levels > 0) TURPY_HIP(enqueue_sh(pl, seed, static_cast<uint32_t>(t), w, st), "screen_generate: sh");
   int ready = -1;
   for (int s = 0; s < pl->M; ++s) {
@@ -485,7 +490,7 @@ turpy_status propagate_impl(turpy_plan* pl, uint64_t seed, int64_t t, const void
     return fail(TURPY_E_WORKSPACE, "propagate: workspace %zu < %zu bytes", ws_bytes, pl->ws_forward());
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (turpy_status s_ = check_capture(pl, st, "propagate")) return s_;
-  Ws w = carve(pl, ws);
+  Ws w = carve(pl, ws, src);
   keep_screens(pl, checkpoints, src, &w);
   const int n = pl->n, M = pl->M;
   const float inv_n = 1.0f / n;
@@ -663,7 +668,7 @@ static turpy_status backward_checkpointed(turpy_plan* pl, uint64_t seed, int64_t
   if (!ws || ws_bytes < pl->ws_backward())
     return fail(TURPY_E_WORKSPACE, "propagate_backward: workspace %zu < %zu bytes", ws_bytes, pl->ws_backward());
   hipStream_t st = static_cast<hipStream_t>(stream);
-  Ws w = carve(pl, ws);
+  Ws w = carve(pl, ws, src);
   keep_screens(pl, const_cast<void*>(checkpoints), src, &w);
   const bool stored = w.screens != nullptr;  // the forward pass kept the screens' column halves
   const float inv_n = 1.0f / n;
@@ -785,7 +790,7 @@ static turpy_status backward_reversible(turpy_plan* pl, uint64_t seed, int64_t t
     return fail(TURPY_E_WORKSPACE, "propagate_backward_reversible: workspace %zu < %zu bytes", ws_bytes,
                 pl->ws_reversible());
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const Ws w = carve(pl, ws);
+  const Ws w = carve(pl, ws, src);
   const float inv_n = 1.0f / n;
   const bool shared = grad_u_in && grad_u_in_stride == 0;
   float2* g = grad_u_in && !shared ? static_cast<float2*>(grad_u_in) : w.gbuf;
@@ -1401,7 +1406,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
   const bool need_rb = screens && (force || !cached(rb, &e));
   if (need_col || need_synth || need_ar || need_rf || need_rb)
     TURPY_HIP(hipMemsetAsync(ws, 0, pl->ws_tune(), st), "plan_tune: clear workspace");
-  const Ws wsp = carve(pl, ws);
+  const Ws wsp = carve(pl, ws, TURPY_SCREENS_SYNTH);
   const int n = pl->n;
   const int64_t plane = static_cast<int64_t>(n) * n;
   if (need_col) {
@@ -1432,6 +1437,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
     const EvolveStep ev{0.99, 0.5, 0.25};
     float2* second = reinterpret_cast<float2*>(static_cast<char*>(ws) + pl->off_ubuf());
     SynthArgs a = synth_args(pl, 0, 1, 0, 1, wsp.gbuf, wsp, &ev);
+    a.solo = 0;
     a.t_dev = nullptr;
     a.M = 1;
     bool flip = false;

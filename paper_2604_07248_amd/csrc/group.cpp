@@ -143,6 +143,7 @@ turpy_status group_create(std::vector<GroupMember> members, Group** out) {
     Ws w{};
     w.scratch = off_ptr<float2>(b);
     w.sh = off_ptr<float2>(b + align_up(static_cast<size_t>(pl->P) * pl->plane_bytes()));
+    w.solo = pl->solo();
     return w;
   };
   auto field = [&](size_t k) { return off_ptr<float2>(members[k].field_bytes); };

@@ -60,6 +60,55 @@ __device__ __forceinline__ void load_field_row(float2 (&v)[kE], const float2* p,
   }
 }
 
+// Subharmonics and piston (Eq. 2-3) added to screen row i0 of pair j after its
+// inverse transform.  Solo: z holds the real screen's rows i0 (re) and
+// i0 + N/2 (im), and both take the real part of the subharmonic field.
+template <int N>
+__device__ __forceinline__ void add_subharmonics(const RowArgs& a, int64_t j, int i0, int t, float2 (&z)[kE]) {
+  constexpr int T = N / kE;
+  if (a.sh_levels <= 0) return;
+  const float2* c = a.sh + (static_cast<size_t>(j) * a.M + a.screen) * 32;
+  float2 mean = c_scale(c[24], a.sh_scale);
+  if (a.solo) mean.y = mean.x;
+#pragma unroll
+  for (int m = 0; m < kE; ++m) z[m] = c_sub(z[m], mean);
+  for (int p = 0; p < a.sh_levels; ++p) {
+    const float2* cp = c + 8 * p;
+    const float2* ph = a.sh_phasor + static_cast<size_t>(p) * N;
+    // the level's field along row `row`: d0 + sa ex.re + i sb ex.im
+    float2 d0, sa, sb;
+    auto along = [&](int row) {
+      const float2 ey = ph[row];
+      const float2 eyc = make_float2(ey.x, -ey.y);
+      // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
+      const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
+      d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
+      const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
+      sa = c_add(dp, dm);
+      sb = c_sub(dp, dm);
+    };
+    float2 e0, ea, eb;
+    if (a.solo) {
+      along(i0 + N / 2);
+      e0 = make_float2(0.0f, d0.x);
+      ea = make_float2(0.0f, sa.x);
+      eb = make_float2(-sb.y, 0.0f);
+      along(i0);
+    } else {
+      along(i0);
+      e0 = d0;
+      ea = sa;
+      eb = sb;
+    }
+#pragma unroll
+    for (int m = 0; m < kE; ++m) {
+      const float2 ex = (ph + t)[T * m];
+      z[m].x += d0.x + sa.x * ex.x - sb.y * ex.y;
+      z[m].y += e0.y + ea.y * ex.x + eb.x * ex.y;
+    }
+  }
+}
+
 // ---------------------------------------------------------------------------
 // Row pass.
 // ---------------------------------------------------------------------------
@@ -87,30 +136,7 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
 #pragma unroll
     for (int m = 0; m < kE; ++m) z[m] = (src + t)[T * m];
     fft<N, kE, true, WV>(z, lds, t, tw);
-    if (a.sh_levels > 0) {
-      const float2* c = a.sh + (static_cast<size_t>(j) * a.M + a.screen) * 32;
-      const float2 mean = c_scale(c[24], a.sh_scale);
-#pragma unroll
-      for (int m = 0; m < kE; ++m) z[m] = c_sub(z[m], mean);
-      for (int p = 0; p < a.sh_levels; ++p) {
-        const float2* cp = c + 8 * p;
-        const float2* ph = a.sh_phasor + static_cast<size_t>(p) * N;
-        const float2 ey = ph[i0];
-        const float2 eyc = make_float2(ey.x, -ey.y);
-        // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
-        const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
-        const float2 d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
-        const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
-        const float2 sa = c_add(dp, dm);
-        const float2 sb = c_sub(dp, dm);
-#pragma unroll
-        for (int m = 0; m < kE; ++m) {
-          const float2 ex = (ph + t)[T * m];
-          z[m].x += d0.x + sa.x * ex.x - sb.y * ex.y;
-          z[m].y += d0.y + sa.y * ex.x + sb.x * ex.y;
-        }
-      }
-    }
+    add_subharmonics<N>(a, j, i0, t, z);
 #pragma unroll
     for (int m = 0; m < kE; ++m) {
       pa[m] = z[m].x;
@@ -240,7 +266,7 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
   const int t = threadIdx.x % T;
   const int i0 = blockIdx.x * G + g;
   const int64_t j = blockIdx.y;
-  const bool has_b = 2 * j + 1 < a.R;
+  const bool has_b = a.solo || 2 * j + 1 < a.R;
   const int64_t r = (role == 1 && has_b) ? 2 * j + 1 : 2 * j;
   const bool writes = role == 0 || has_b;
   const RowLds lds{smem + (role * G + g) * RowLds::words(N)};
@@ -248,6 +274,8 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
   __shared__ float2 tw_lds[N];
   const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
+  const size_t rplane = a.solo ? plane / 2 : plane;  // from one realization's rows to the next's
+  const int64_t in_stride = a.solo ? static_cast<int64_t>(rplane) : a.in_stride;
   const size_t row_off = static_cast<size_t>(i0) * N;
   const bool in_spec = a.in_spectral != 0, out_spec = a.out_spectral != 0;
 
@@ -258,8 +286,9 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
   // transform that precedes its use in the screen gradient
   float2 wck[kE];
   const bool want_ck = BWD && a.grad_screens && writes;
-  const size_t ck_row = (static_cast<size_t>(r) * a.M + a.screen) * plane + row_off;
-  const size_t cw_row = a.ckpt_single ? static_cast<size_t>(r) * plane + row_off : ck_row;
+  const size_t ck_row = a.solo ? static_cast<size_t>(a.screen) * plane + static_cast<size_t>(r) * rplane + row_off
+                               : (static_cast<size_t>(r) * a.M + a.screen) * plane + row_off;
+  const size_t cw_row = a.ckpt_single ? static_cast<size_t>(r) * rplane + row_off : ck_row;
   auto fetch_ckpt = [&]() {
     if constexpr (BWD) {
       if (want_ck) {
@@ -275,8 +304,8 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
 #pragma unroll
       for (int m = 0; m < kE; ++m) x[m] = ld_s<true>(src + t + T * m);
       {
-        const float2* fa = a.in + r * a.in_stride + row_off;
-        load_field_row<true, T>(y, fa + t, a.in_stride == 0);
+        const float2* fa = a.in + r * in_stride + row_off;
+        load_field_row<true, T>(y, fa + t, in_stride == 0);
       }
       fft<N, kE, true, WV>(x, lds, t, tw);
     } else {
@@ -287,8 +316,8 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
       if (in_spec) idle_fft<N, WV>();
     }
   } else {
-    const float2* src = a.in + r * a.in_stride + row_off;
-    load_field_row<true, T>(x, src + t, a.in_stride == 0);
+    const float2* src = a.in + r * in_stride + row_off;
+    load_field_row<true, T>(x, src + t, in_stride == 0);
     fetch_ckpt();
     if (in_spec) {
       if (a.pre) {
@@ -308,30 +337,7 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
   if constexpr (SCREEN == ROW_SCRATCH) {
     __syncthreads();
     if (role == 0) {
-      if (a.sh_levels > 0) {
-        const float2* c = a.sh + (static_cast<size_t>(j) * a.M + a.screen) * 32;
-        const float2 mean = c_scale(c[24], a.sh_scale);
-#pragma unroll
-        for (int m = 0; m < kE; ++m) x[m] = c_sub(x[m], mean);
-        for (int p = 0; p < a.sh_levels; ++p) {
-          const float2* cp = c + 8 * p;
-          const float2* phs = a.sh_phasor + static_cast<size_t>(p) * N;
-          const float2 ey = phs[i0];
-          const float2 eyc = make_float2(ey.x, -ey.y);
-          // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
-          const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
-          const float2 d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
-          const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
-          const float2 sa = c_add(dp, dm);
-          const float2 sb = c_sub(dp, dm);
-#pragma unroll
-          for (int m = 0; m < kE; ++m) {
-            const float2 ex = (phs + t)[T * m];
-            x[m].x += d0.x + sa.x * ex.x - sb.y * ex.y;
-            x[m].y += d0.y + sa.y * ex.x + sb.x * ex.y;
-          }
-        }
-      }
+      add_subharmonics<N>(a, j, i0, t, x);
 #pragma unroll
       for (int m = 0; m < kE; ++m) {
         ph[m] = x[m].x;
@@ -397,7 +403,7 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
       }
     }
     if (writes) {
-      float2* dst = a.out + r * static_cast<int64_t>(plane) + row_off;
+      float2* dst = a.out + r * static_cast<int64_t>(rplane) + row_off;
 #pragma unroll
       for (int m = 0; m < kE; ++m) (dst + t)[T * m] = x[m];
     }
@@ -409,8 +415,8 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
 #pragma unroll
       for (int m = 0; m < kE; ++m) x[m] = y[m];
     } else {
-      const float2* src = a.in + r * a.in_stride + row_off;
-      load_field_row<true, T>(x, src + t, a.in_stride == 0);
+      const float2* src = a.in + r * in_stride + row_off;
+      load_field_row<true, T>(x, src + t, in_stride == 0);
     }
     fetch_ckpt();
     if (in_spec) {
@@ -477,7 +483,7 @@ __device__ __forceinline__ void row_relay_body(const RowArgs& a) {
   const int g = (threadIdx.x % HALF) / T;
   const int t = threadIdx.x % T;
   const int64_t j = blockIdx.y;
-  const bool has_b = 2 * j + 1 < a.R;
+  const bool has_b = a.solo || 2 * j + 1 < a.R;
   const int64_t ra = 2 * j, rb = has_b ? 2 * j + 1 : 2 * j;  // a missing B reads A's rows, writes nothing
   const int row0 = blockIdx.x * 2 * G + g;  // this thread's row in group 0
   const int row1 = row0 + G;                // and in group 1
@@ -485,14 +491,16 @@ __device__ __forceinline__ void row_relay_body(const RowArgs& a) {
   float* hand = handoff_rows + g * N + t;
   const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
+  const size_t rplane = a.solo ? plane / 2 : plane;  // from one realization's rows to the next's
+  const int64_t in_stride = a.solo ? static_cast<int64_t>(rplane) : a.in_stride;
   const bool in_spec = a.in_spectral != 0, out_spec = a.out_spectral != 0;
   const bool both = in_spec || out_spec;
 
   float ph[kE];
   float2 x[kE], y[kE];
   auto load_field = [&](float2 (&v)[kE], int64_t r, int row) {
-    const float2* src = a.in + r * a.in_stride + static_cast<size_t>(row) * N + t;
-    load_field_row<true, T>(v, src, a.in_stride == 0);
+    const float2* src = a.in + r * in_stride + static_cast<size_t>(row) * N + t;
+    load_field_row<true, T>(v, src, in_stride == 0);
   };
   // x (a loaded field row) to real space; slot: the other worker transforms
   // in this stage
@@ -512,30 +520,7 @@ __device__ __forceinline__ void row_relay_body(const RowArgs& a) {
   // subharmonics and the piston of Eq. 2-3; Re into ph, Im into the hand-off
   auto screen = [&](int row) {
     fft<N, kE, true, WV>(x, lds, t, tw);
-    if (a.sh_levels > 0) {
-      const float2* c = a.sh + (static_cast<size_t>(j) * a.M + a.screen) * 32;
-      const float2 mean = c_scale(c[24], a.sh_scale);
-#pragma unroll
-      for (int m = 0; m < kE; ++m) x[m] = c_sub(x[m], mean);
-      for (int p = 0; p < a.sh_levels; ++p) {
-        const float2* cp = c + 8 * p;
-        const float2* phs = a.sh_phasor + static_cast<size_t>(p) * N;
-        const float2 ey = phs[row];
-        const float2 eyc = make_float2(ey.x, -ey.y);
-        // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
-        const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
-        const float2 d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
-        const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
-        const float2 sa = c_add(dp, dm);
-        const float2 sb = c_sub(dp, dm);
-#pragma unroll
-        for (int m = 0; m < kE; ++m) {
-          const float2 ex = (phs + t)[T * m];
-          x[m].x += d0.x + sa.x * ex.x - sb.y * ex.y;
-          x[m].y += d0.y + sa.y * ex.x + sb.x * ex.y;
-        }
-      }
-    }
+    add_subharmonics<N>(a, j, row, t, x);
 #pragma unroll
     for (int m = 0; m < kE; ++m) {
       ph[m] = x[m].x;
@@ -561,7 +546,7 @@ __device__ __forceinline__ void row_relay_body(const RowArgs& a) {
       idle_fft<N, WV>();
     }
     if (writes) {
-      float2* dst = a.out + r * static_cast<int64_t>(plane) + static_cast<size_t>(row) * N + t;
+      float2* dst = a.out + r * static_cast<int64_t>(rplane) + static_cast<size_t>(row) * N + t;
 #pragma unroll
       for (int m = 0; m < kE; ++m) dst[T * m] = x[m];
     }
@@ -777,6 +762,93 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a, int slot) {
 template <int N, int K, int R2SEL>
 __global__ __launch_bounds__(K * (N / kE))
 void synth_col_kernel(SynthArgs a) { synth_col_body<N, K, R2SEL>(a, blockIdx.y); }
+
+// ---------------------------------------------------------------------------
+// The synthesis for one realization, which has no use for the imaginary part
+// of its complex screen.  Re z is the transform of the Hermitian part
+// h(k) = (c(k) + conj c(-k)) / 2, whose column transforms C obey
+// C(y, -k1) = conj C(y, k1): half of the columns are transformed.  Both bins'
+// noise is still drawn (the screen is the pair's Re z), but the weight is
+// computed once for the two.  A block is K columns k1 < N/2; it writes the
+// rows y and y + N/2 packed into one complex row, Z(y, k1) = C(y, k1) +
+// i C(y + N/2, k1), at the columns k1 and N - k1, so that the row pass
+// transforms N/2 rows and reads N^2/2 words instead of N^2.  The columns 0 and
+// N/2 (real C) share one transform in a block of their own, block 0, whose K
+// threads per row divide its noise among them.
+// Bound by the arithmetic, most of it Philox.
+// ---------------------------------------------------------------------------
+template <int N, int K, int R2SEL>
+__device__ __forceinline__ void synth_solo_body(const SynthArgs& a, int slot) {
+  constexpr int T = N / kE;
+  constexpr int H = N / 2;
+  static_assert(K <= H && K >= 2, "the edge block keeps two columns in a strip's LDS");
+  __shared__ float2 smem[ColLds<K>::words(N)];
+  TURPY_LDS_INIT(smem);
+  __shared__ float2 tw_lds[N];
+  const bool edge = blockIdx.x == 0;
+  const int strip = edge ? 0 : static_cast<int>(xcd_remap(blockIdx.x - 1, H / K));
+  const int c = threadIdx.x % K;
+  const int t = threadIdx.x / K;
+  const int k1 = strip * K + c;
+  const ColLds<K> lds{smem, c};
+  const uint32_t screen = a.screen + static_cast<uint32_t>(slot);
+  const float amp = 0.5f * a.amp[slot];
+  // h at the bins (k0, col) and (k0 + N/2, col), k0 < N/2, col <= N/2
+  auto pair_bins = [&](int k0, int col, float2* lo, float2* hi) {
+    const int mirror = (N - col) & (N - 1);
+    const int back = k0 == 0 ? 0 : H - k0;  // block row of the bins -k0 and N/2 - k0
+    const uint4 v = philox4x32_10(noise_counter(static_cast<uint32_t>(k0) * N + col, time_step(a), 0, a.tag, screen),
+                                  a.key0, a.key1);
+    uint4 u = philox4x32_10(noise_counter(static_cast<uint32_t>(back) * N + mirror, time_step(a), 0, a.tag, screen),
+                            a.key0, a.key1);
+    if (k0 == 0) u = make_uint4(u.z, u.w, u.x, u.y);
+    const float2 n_lo = box_muller(v.x, v.y), p_lo = box_muller(u.z, u.w);
+    const float2 n_hi = box_muller(v.z, v.w), p_hi = box_muller(u.x, u.y);
+    const int kx = col;  // its square is the signed bin's
+    const float w_lo = psd_amp(k0 * k0 + kx * kx, amp, a.df2, a.inner, a.f02, a.q);
+    const float w_hi = psd_amp((k0 - H) * (k0 - H) + kx * kx, amp, a.df2, a.inner, a.f02, a.q);
+    *lo = make_float2((n_lo.x + p_lo.x) * w_lo, (n_lo.y - p_lo.y) * w_lo);
+    *hi = make_float2((n_hi.x + p_hi.x) * w_hi, (n_hi.y - p_hi.y) * w_hi);
+  };
+  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  float2 x[kE];
+  if (!edge) {
+#pragma unroll
+    for (int m = 0; m < kE / 2; ++m) pair_bins(t + T * m, k1, &x[m], &x[m + kE / 2]);
+  } else {
+    for (int i = c; i < kE; i += K) {  // (column 0 or N/2, element) items of this row
+      const int sel = i / (kE / 2), k0 = t + T * (i % (kE / 2));
+      pair_bins(k0, sel ? H : 0, &smem[sel * N + k0], &smem[sel * N + k0 + H]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kE; ++m) {  // h(., 0) + i h(., N/2), the same in every column
+      const float2 p = smem[t + T * m], q = smem[N + t + T * m];
+      x[m] = make_float2(p.x - q.y, p.y + q.x);
+    }
+    __syncthreads();
+  }
+  fft<N, kE, true, false, R2SEL>(x, lds, t, tw);
+  float2* dst = a.scratch + slot * a.screen_stride + static_cast<size_t>(t) * N;
+#pragma unroll
+  for (int m = 0; m < kE / 2; ++m) {
+    const float2 p = x[m], q = x[m + kE / 2];  // C (or C0 + i C_N/2) at y and y + N/2
+    float2* row = dst + static_cast<size_t>(T * m) * N;
+    if (edge) {
+      if (c == 0) {
+        row[0] = make_float2(p.x, q.x);
+        row[H] = make_float2(p.y, q.y);
+      }
+    } else if (k1 != 0) {
+      row[k1] = make_float2(p.x - q.y, p.y + q.x);
+      row[N - k1] = make_float2(p.x + q.y, q.x - p.y);
+    }
+  }
+}
+
+template <int N, int K, int R2SEL>
+__global__ __launch_bounds__(K * (N / kE))
+void synth_solo_kernel(SynthArgs a) { synth_solo_body<N, K, R2SEL>(a, blockIdx.y); }
 
 // ---------------------------------------------------------------------------
 // Subharmonic coefficients of Eq. 2 for every (pair, screen), and their mean.
@@ -1438,17 +1510,14 @@ __global__ __launch_bounds__(256) void copy_kernel(const float2* in, int64_t in_
 constexpr int kRowWaves = 3;
 constexpr bool row_waves_built(int n, int w) { return w == kRowWaves || (n >= 256 && (w == 2 || w == 4)); }
 
-// A forward screen pass of a single realization where the relay schedule is
-// not built (N > 1024): the pair schedule would leave half of every block
+// A forward screen pass of a single realization on full scratch planes (an AR
+// state, or screens kept with the checkpoints) where the relay schedule is not
+// built (N > 1024): the pair schedule would leave half of every block
 // transforming rows nobody keeps, so one group of threads per row takes it
-// (serving mix: the 252 instances at N = 2048 274 -> 213 ms forward; all 4096
-// forward + adjoint with checkpoints 3.11 -> 2.94 s).  At N <= 1024 the relay
-// schedule stays, and in the adjoint the pair schedule (one group per row
-// measured 3.11 -> 3.28 s there).
+// (252 such instances at N = 2048 274 -> 213 ms forward).
 template <int N>
-constexpr bool solo_forward(int64_t R, int backward, const void* ckpt) {
-  (void)ckpt;
-  return N > 1024 && R == 1 && !backward;
+bool solo_forward(const RowArgs& a) {
+  return N > 1024 && a.R == 1 && !a.backward && !a.solo;
 }
 
 // The relay kernel for forward passes with synthesised screens and no
@@ -1460,7 +1529,7 @@ constexpr bool solo_forward(int64_t R, int backward, const void* ckpt) {
 template <int N, int W>
 void relay_launch_w(const RowArgs& a, int64_t pairs, hipStream_t s) {
   constexpr int WB = row_waves_built(N, W) ? W : kRowWaves;
-  const dim3 grid(N / (2 * relay_rows<N>()), static_cast<uint32_t>(pairs));
+  const dim3 grid((a.solo ? N / 2 : N) / (2 * relay_rows<N>()), static_cast<uint32_t>(pairs));
   hipLaunchKernelGGL((row_relay_kernel<N, WB>), grid, dim3(relay_block<N>()), 0, s, a);
 }
 
@@ -1470,6 +1539,7 @@ bool relay_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
     return false;
   } else {
     if (a.screen_mode != ROW_SCRATCH || a.backward || a.conj_tables || a.ckpt_out || a.pre) return false;
+    if (a.solo && 2 * relay_rows<N>() > N / 2) return false;
     switch (a.waves ? a.waves : kRowWaves) {
       case 2: relay_launch_w<N, 2>(a, pairs, s); break;
       case 4: relay_launch_w<N, 4>(a, pairs, s); break;
@@ -1483,7 +1553,7 @@ template <int N, int SCREEN, bool BWD, int W>
 void pair_launch_w(const RowArgs& a, int64_t pairs, hipStream_t s) {
   constexpr int WB = row_waves_built(N, W) && SCREEN == ROW_SCRATCH ? W : kRowWaves;
   constexpr int GP = pair_rows<N>();
-  const dim3 pgrid(N / GP, static_cast<uint32_t>(pairs));
+  const dim3 pgrid((a.solo ? N / 2 : N) / GP, static_cast<uint32_t>(pairs));
   hipLaunchKernelGGL((row_pair_kernel<N, SCREEN, BWD, WB>), pgrid, dim3(pair_block<N>()), 0, s, a);
 }
 
@@ -1502,7 +1572,7 @@ hipError_t row_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
   dim3 block(row_block<N>());
   if (a.screen_mode == ROW_NO_SCREEN)
     hipLaunchKernelGGL((row_pass_kernel<N, ROW_NO_SCREEN, false>), grid, block, 0, s, a);
-  else if (a.phase_out || (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(a.R, a.backward, a.ckpt_out)) {
+  else if (a.phase_out || (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(a)) {
     // screen output, grids too small for the two halves to sit in separate
     // waves, or a single realization on the pair schedule
     if (a.screen_mode == ROW_SCRATCH && !a.backward)
@@ -1573,6 +1643,14 @@ hipError_t synth_launch_kr(const SynthArgs& a, hipStream_t s) {
   if constexpr (!strip_fits<N, K>() || !radix_built(N, R2SEL)) {
     return hipErrorInvalidValue;
   } else {
+    if (a.solo) {
+      if constexpr (solo_fits(N) && K <= N / 2) {
+        hipLaunchKernelGGL((synth_solo_kernel<N, K, R2SEL>), dim3(N / 2 / K + 1, a.count), dim3(K * (N / kE)), 0, s, a);
+        return hipGetLastError();
+      } else {
+        return hipErrorInvalidValue;
+      }
+    }
     const uint64_t blocks = static_cast<uint64_t>(N / K) * a.P;
     hipLaunchKernelGGL((synth_col_kernel<N, K, R2SEL>), dim3(static_cast<uint32_t>(blocks), a.count),
                        dim3(K * (N / kE)), 0, s, a);
@@ -1681,14 +1759,15 @@ __global__ __launch_bounds__(col_width<N>() * (N / kE)) void col_pass_group_kern
   col_pass_body<N, ANGULAR, col_width<N>(), R2SEL>(a);
 }
 
-template <int N, int R2SEL>
+template <int N, int R2SEL, bool SOLO>
 __global__ __launch_bounds__(synth_width<N>() * (N / kE)) void synth_group_kernel(const SynthArgs* tab, GroupCall g) {
   SynthArgs a = tab[blockIdx.y];
   a.scratch = rebase(g.ws, a.scratch);
   group_key(g, &a.key0, &a.key1);
   a.t = g.t;
   a.t_dev = g.t_dev;
-  synth_col_body<N, synth_width<N>(), R2SEL>(a, 0);
+  if constexpr (SOLO) synth_solo_body<N, synth_width<N>(), R2SEL>(a, 0);
+  else synth_col_body<N, synth_width<N>(), R2SEL>(a, 0);
 }
 
 __global__ __launch_bounds__(64) void sh_group_kernel(const ShArgs* tab, GroupCall g) {
@@ -1710,7 +1789,8 @@ hipError_t row_group_launch(const RowArgs& proto, const RowArgs* tab, uint32_t c
   const uint32_t P = static_cast<uint32_t>(pairs);
   // halves that are not whole waves, or a single realization on the pair
   // schedule: one group of threads per row (as row_launch chooses)
-  const bool small = (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(proto.R, proto.backward, g.ck);
+  const bool small = (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(proto);
+  const uint32_t rows = proto.solo ? N / 2 : N;
   if (proto.phase_out) return hipErrorInvalidValue;
   if (proto.screen_mode == ROW_NO_SCREEN) {
     hipLaunchKernelGGL((row_pass_group_kernel<N, ROW_NO_SCREEN>), dim3(N / G, P, count), dim3(row_block<N>()), 0,
@@ -1721,7 +1801,7 @@ hipError_t row_group_launch(const RowArgs& proto, const RowArgs* tab, uint32_t c
     if (small)
       hipLaunchKernelGGL((row_pass_group_bwd_kernel<N>), dim3(N / G, P, count), dim3(row_block<N>()), 0, s, tab, g);
     else
-      hipLaunchKernelGGL((row_pair_group_bwd_kernel<N>), dim3(N / pair_rows<N>(), P, count), dim3(pair_block<N>()),
+      hipLaunchKernelGGL((row_pair_group_bwd_kernel<N>), dim3(rows / pair_rows<N>(), P, count), dim3(pair_block<N>()),
                          0, s, tab, g);
   } else if (small) {
     hipLaunchKernelGGL((row_pass_group_kernel<N, ROW_SCRATCH>), dim3(N / G, P, count), dim3(row_block<N>()), 0, s,
@@ -1729,14 +1809,14 @@ hipError_t row_group_launch(const RowArgs& proto, const RowArgs* tab, uint32_t c
   } else {
     bool relay = false;
     if constexpr (relay_fits<N>() && N <= 1024) {
-      if (!g.ck && !proto.conj_tables && !proto.pre) {
-        hipLaunchKernelGGL((row_relay_group_kernel<N>), dim3(N / (2 * relay_rows<N>()), P, count),
+      if (!g.ck && !proto.conj_tables && !proto.pre && 2 * relay_rows<N>() <= static_cast<int>(rows)) {
+        hipLaunchKernelGGL((row_relay_group_kernel<N>), dim3(rows / (2 * relay_rows<N>()), P, count),
                            dim3(relay_block<N>()), 0, s, tab, g);
         relay = true;
       }
     }
     if (!relay)
-      hipLaunchKernelGGL((row_pair_group_kernel<N>), dim3(N / pair_rows<N>(), P, count), dim3(pair_block<N>()), 0, s,
+      hipLaunchKernelGGL((row_pair_group_kernel<N>), dim3(rows / pair_rows<N>(), P, count), dim3(pair_block<N>()), 0, s,
                          tab, g);
   }
   return hipGetLastError();
@@ -1775,8 +1855,18 @@ hipError_t synth_group_launch_r(const SynthArgs& proto, const SynthArgs* tab, ui
   if constexpr (!radix_built(N, R2SEL)) {
     return hipErrorInvalidValue;
   } else {
+    const dim3 block(synth_width<N>() * (N / kE));
+    if (proto.solo) {
+      if constexpr (solo_fits(N)) {
+        hipLaunchKernelGGL((synth_group_kernel<N, R2SEL, true>), dim3(N / 2 / synth_width<N>() + 1, count), block, 0, s,
+                           tab, g);
+        return hipGetLastError();
+      } else {
+        return hipErrorInvalidValue;
+      }
+    }
     const dim3 grid(static_cast<uint32_t>((N / synth_width<N>()) * proto.P), count);
-    hipLaunchKernelGGL((synth_group_kernel<N, R2SEL>), grid, dim3(synth_width<N>() * (N / kE)), 0, s, tab, g);
+    hipLaunchKernelGGL((synth_group_kernel<N, R2SEL, false>), grid, block, 0, s, tab, g);
     return hipGetLastError();
   }
 }

@@ -29,7 +29,7 @@ struct RowArgs {
   int conj_tables;          // use conj(pre), conj(post)
   float scale;              // normalisation folded into the pointwise step
   int screen_mode;          // RowScreen
-  const float2* scratch;    // [P][N][N] column-transformed complex screen, revolutions
+  const float2* scratch;    // [P][N][N] column-transformed complex screen, revolutions (solo: [N/2][N])
   const float* screens;     // [R][M][N][N] radians (materialised)
   int screen;               // screen index s
   int M;                    // screens per path
@@ -44,6 +44,9 @@ struct RowArgs {
   float* grad_screens;      // backward: [R][M][N][N] dL/dphi, or NULL
   float* phase_out;         // [R][M][N][N] radians: write the screens themselves, or NULL
   int waves;                // occupancy hint of the screen row passes (2, 3, 4; 0: the default)
+  // One realization with solo scratch (SynthArgs::solo): its rows y and
+  // y + N/2 take the places of a pair's two realizations, N/2 rows apiece
+  int solo;
 };
 
 struct ColArgs {
@@ -97,6 +100,10 @@ struct SynthArgs {
   uint32_t ar_tag;          // innovation tag
   float alpha_f, blend;     // alpha and sqrt(1 - alpha^2), rounded from FP64
   double sx, sy;            // frozen-flow shift in pixels
+  // One realization (P = 1, noise source): only the real screen is
+  // synthesised, rows y and y + N/2 as the real and imaginary part of one
+  // complex row: scratch [N/2][N]
+  int solo;
 };
 
 struct ShArgs {

@@ -89,6 +89,10 @@ constexpr int relay_block() { return 2 * relay_rows<N>() * (N / kE); }
 template <int N>
 constexpr bool relay_fits() { return (relay_rows<N>() * (N / kE)) % 64 == 0; }
 
+// Grids on which a single realization's real screen is synthesised on its own
+// (SynthArgs::solo): the row passes' halves must be whole waves on N/2 rows.
+constexpr bool solo_fits(int n) { return n >= 64; }
+
 // Spread a 1-D block index so that consecutive logical tiles land on the same
 // XCD (blocks are dealt round-robin over the 8 XCDs, each with its own L2).
 __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nb) {

@@ -148,6 +148,7 @@ struct turpy_plan {
   bool screen_ck = false;        // TURPY_SCREEN_CHECKPOINTS: checkpoints keep the screens' column halves
   std::string arch;              // device architecture (tuning-cache key)
 
+  bool solo() const { return R == 1 && turpy::solo_fits(n); }
   size_t plane_bytes() const { return static_cast<size_t>(n) * n * sizeof(float2); }
   // scratch: the column halves of as many screens as fit kBatchScratch, at least one
   size_t scratch_bytes() const {
@@ -184,17 +185,22 @@ struct Ws {
   // screens synthesised by one launch: those with the same s / batch, screen s
   // in slot s % batch of the scratch
   int batch = 1;
+  // one realization: real screens, two rows to a complex one ([N/2][N] each)
+  bool solo = false;
   float2* screen(int s) const {
     return screens ? screens + static_cast<size_t>(s) * screen_stride
                    : scratch + static_cast<size_t>(s % batch) * screen_stride;
   }
 };
 
-inline Ws carve(const turpy_plan* pl, void* ws) {
+// For a call that takes its screens from `src`: synthesised screens of a
+// single realization are held two real rows to a complex one.
+inline Ws carve(const turpy_plan* pl, void* ws, int32_t src) {
   char* b = static_cast<char*>(ws);
   Ws w{reinterpret_cast<float2*>(b), reinterpret_cast<float2*>(b + pl->off_sh()),
        reinterpret_cast<float2*>(b + pl->off_src()), reinterpret_cast<float2*>(b + pl->off_gbuf())};
-  w.screen_stride = static_cast<size_t>(pl->P) * pl->n * pl->n;
+  w.solo = src == TURPY_SCREENS_SYNTH && pl->solo();
+  w.screen_stride = static_cast<size_t>(pl->P) * pl->n * pl->n / (w.solo ? 2 : 1);
   w.batch = std::max(1, std::min({pl->M, kSynthScreens,
                                   static_cast<int>(pl->scratch_bytes() / (w.screen_stride * sizeof(float2)))}));
   return w;
@@ -259,6 +265,7 @@ inline SynthArgs synth_args(const turpy_plan* pl, uint64_t seed, uint32_t t, int
   a.scratch = w.screen(s);
   a.screen_stride = w.screen_stride;
   a.count = count;
+  a.solo = w.solo ? 1 : 0;
   a.P = pl->P;
   key_of(seed, &a.key0, &a.key1);
   a.t = t;
@@ -320,6 +327,7 @@ inline turpy_status screen_fields(const turpy_plan* pl, int32_t src, const void*
   } else {
     a->screen_mode = ROW_SCRATCH;
     a->scratch = w.screen(s);
+    a->solo = w.solo ? 1 : 0;
     a->sh_levels = pl->sh_levels;
     if (src == TURPY_SCREENS_SYNTH) {
       a->sh = w.sh;
