@@ -23,7 +23,7 @@ namespace turpy {
 template <bool INV>
 __device__ __forceinline__ float2 c_rot(float2 a, float c, float s) {
   const float sn = INV ? s : -s;
-  return make_float2(a.x * c - a.y * sn, a.x * sn + a.y * c);
+  return make_float2(__builtin_fmaf(a.x, c, -(a.y * sn)), __builtin_fmaf(a.x, sn, a.y * c));
 }
 // multiply by -i (forward) or +i (inverse)
 template <bool INV>

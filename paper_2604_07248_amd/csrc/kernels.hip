@@ -129,6 +129,8 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
   const size_t plane = static_cast<size_t>(N) * N;
   const size_t row_off = static_cast<size_t>(i0) * N;
 
+  const float sign = a.conj_tables ? -1.0f : 1.0f;  // of the tables' imaginary parts
+
   float pa[kE], pb[kE];  // screen phase (revolutions) for realizations 2j and 2j+1
   if constexpr (SCREEN == ROW_SCRATCH) {
     float2 z[kE];
@@ -180,7 +182,7 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
 #pragma unroll
         for (int m = 0; m < kE; ++m) {
           const float2 h = (a.pre + t)[T * m];
-          x[m] = a.conj_tables ? c_mulc(x[m], h) : c_mul(x[m], h);
+          x[m] = c_mul(x[m], make_float2(h.x, h.y * sign));
         }
       }
       fft<N, kE, true, WV>(x, lds, t, tw);
@@ -231,7 +233,7 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
 #pragma unroll
         for (int m = 0; m < kE; ++m) {
           const float2 h = (a.post + t)[T * m];
-          x[m] = a.conj_tables ? c_mulc(x[m], h) : c_mul(x[m], h);
+          x[m] = c_mul(x[m], make_float2(h.x, h.y * sign));
         }
       }
     }
@@ -243,6 +245,61 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
 
 template <int N, int SCREEN, bool BWD>
 __global__ __launch_bounds__(row_block<N>()) void row_pass_kernel(RowArgs a) { row_pass_body<N, SCREEN, BWD>(a); }
+
+// The end of a screen row: the pointwise step of Eq. 1 (or its adjoint) at the
+// phases ph, the checkpoint, the forward transform and the store (none of the
+// stores without `writes`).
+template <int N, bool BWD>
+__device__ __forceinline__ void finish_row(const RowArgs& a, float2 (&x)[kE], const float (&ph)[kE],
+                                           const float2 (&wck)[kE], bool want_ck, bool writes, size_t ck, size_t cw,
+                                           float2* dst, const RowLds& lds, int t, const float2* tw) {
+  constexpr int T = N / kE;
+  constexpr bool WV = T <= 64;
+  if constexpr (!BWD) {
+#pragma unroll
+    for (int m = 0; m < kE; ++m) {
+      float s, c;
+      sincos_rev(ph[m], &s, &c);
+      x[m] = c_mul(x[m], make_float2(c * a.scale, s * a.scale));
+    }
+    if (a.ckpt_out && writes) {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) st_s<true>(a.ckpt_out + cw + t + T * m, x[m]);
+    }
+  } else {
+    if (a.ckpt_out && writes) {  // the forward field at this screen, rebuilt by the adjoint chain
+#pragma unroll
+      for (int m = 0; m < kE; ++m) (a.ckpt_out + cw + t)[T * m] = x[m];
+    }
+    if (want_ck) {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) {
+        const float2 w = wck[m];
+        st_f<true>(a.grad_screens + ck + t + T * m, w.x * x[m].y - w.y * x[m].x);  // Im(conj(W) g)
+      }
+    }
+#pragma unroll
+    for (int m = 0; m < kE; ++m) {
+      float s, c;
+      sincos_rev(ph[m], &s, &c);
+      x[m] = c_mul(x[m], make_float2(c * a.scale, -s * a.scale));
+    }
+  }
+  if (a.out_spectral) {
+    fft<N, kE, false, WV>(x, lds, t, tw);
+    if (a.post) {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) {
+        const float2 h = (a.post + t)[T * m];
+        x[m] = BWD ? c_mulc(x[m], h) : c_mul(x[m], h);
+      }
+    }
+  }
+  if (writes) {
+#pragma unroll
+    for (int m = 0; m < kE; ++m) (dst + t)[T * m] = x[m];
+  }
+}
 
 // ---------------------------------------------------------------------------
 // Row pass with a screen, split over the two realizations of a pair.  Half A
@@ -324,7 +381,7 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
 #pragma unroll
         for (int m = 0; m < kE; ++m) {
           const float2 h = (a.pre + t)[T * m];
-          x[m] = a.conj_tables ? c_mulc(x[m], h) : c_mul(x[m], h);
+          x[m] = BWD ? c_mulc(x[m], h) : c_mul(x[m], h);
         }
       }
       fft<N, kE, true, WV>(x, lds, t, tw);
@@ -360,54 +417,8 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
   }
 
   // the pointwise step of Eq. 1 (or its adjoint) and the forward transform
-  auto finish = [&]() {
-    const size_t ck = ck_row, cw = cw_row;
-    if constexpr (!BWD) {
-#pragma unroll
-      for (int m = 0; m < kE; ++m) {
-        float s, c;
-        sincos_rev(ph[m], &s, &c);
-        x[m] = c_mul(x[m], make_float2(c * a.scale, s * a.scale));
-      }
-      if (a.ckpt_out && writes) {
-#pragma unroll
-        for (int m = 0; m < kE; ++m) st_s<true>(a.ckpt_out + cw + t + T * m, x[m]);
-      }
-    } else {
-      if (a.ckpt_out && writes) {  // the forward field at this screen, rebuilt by the adjoint chain
-#pragma unroll
-        for (int m = 0; m < kE; ++m) (a.ckpt_out + cw + t)[T * m] = x[m];
-      }
-      if (want_ck) {
-#pragma unroll
-        for (int m = 0; m < kE; ++m) {
-          const float2 w = wck[m];
-          st_f<true>(a.grad_screens + ck + t + T * m, w.x * x[m].y - w.y * x[m].x);  // Im(conj(W) g)
-        }
-      }
-#pragma unroll
-      for (int m = 0; m < kE; ++m) {
-        float s, c;
-        sincos_rev(ph[m], &s, &c);
-        x[m] = c_mul(x[m], make_float2(c * a.scale, -s * a.scale));
-      }
-    }
-    if (out_spec) {
-      fft<N, kE, false, WV>(x, lds, t, tw);
-      if (a.post) {
-#pragma unroll
-        for (int m = 0; m < kE; ++m) {
-          const float2 h = (a.post + t)[T * m];
-          x[m] = a.conj_tables ? c_mulc(x[m], h) : c_mul(x[m], h);
-        }
-      }
-    }
-    if (writes) {
-      float2* dst = a.out + r * static_cast<int64_t>(rplane) + row_off;
-#pragma unroll
-      for (int m = 0; m < kE; ++m) (dst + t)[T * m] = x[m];
-    }
-  };
+  float2* dst = a.out + r * static_cast<int64_t>(rplane) + row_off;
+  auto finish = [&]() { finish_row<N, BWD>(a, x, ph, wck, want_ck, writes, ck_row, cw_row, dst, lds, t, tw); };
 
   // stage 3: A loads / inverse-transforms its field; B finishes
   if (role == 0) {
@@ -424,7 +435,7 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
 #pragma unroll
         for (int m = 0; m < kE; ++m) {
           const float2 h = (a.pre + t)[T * m];
-          x[m] = a.conj_tables ? c_mulc(x[m], h) : c_mul(x[m], h);
+          x[m] = BWD ? c_mulc(x[m], h) : c_mul(x[m], h);
         }
       }
       fft<N, kE, true, WV>(x, lds, t, tw);
@@ -594,6 +605,93 @@ __global__ __launch_bounds__(relay_block<N>()) __attribute__((amdgpu_waves_per_e
 void row_relay_kernel(RowArgs a) { row_relay_body<N>(a); }
 
 // ---------------------------------------------------------------------------
+// Row pass with a screen, one worker per transform: worker 0 finishes the
+// screen row while workers 1 and 2 inverse-transform the field rows of the
+// pair's realizations; after one hand-over through LDS they modulate and
+// transform forward.  The longest chain of a block is two transforms, against
+// three of the pair schedule and five of the relay's.  A worker is one wave,
+// and worker 0 has nothing to do in the second half, so this is the schedule
+// of launches that do not fill the chip, whose time is the chain and the
+// latency around it (one 256 x 256 realization 13.0 -> 8.2 us forward, 10.9 ->
+// 8.5 us in the adjoint, bracketed by events).
+// ---------------------------------------------------------------------------
+template <int N, bool BWD>
+__device__ __forceinline__ void row_trio_body(const RowArgs& a) {
+  constexpr int T = N / kE;
+  constexpr int G = trio_rows<N>();
+  constexpr int WORKER = G * T;
+  static_assert(WORKER == 64 && G <= N / 2, "a worker is a wave, each transform inside it");
+  __shared__ float2 smem[3 * G * RowLds::words(N)];
+  TURPY_LDS_INIT(smem);
+  __shared__ float2 tw_lds[N];
+  const int role = threadIdx.x / WORKER;
+  const int g = (threadIdx.x % WORKER) / T;
+  const int t = threadIdx.x % T;
+  const int i0 = blockIdx.x * G + g;
+  const int64_t j = blockIdx.y;
+  const bool has_b = a.solo || 2 * j + 1 < a.R;
+  const int64_t r = (role == 2 && has_b) ? 2 * j + 1 : 2 * j;  // a missing B reads A's rows, writes nothing
+  const bool writes = role == 1 || (role == 2 && has_b);
+  const RowLds lds{smem + (role * G + g) * RowLds::words(N)};
+  const RowLds screen_row{smem + g * RowLds::words(N)};
+  const size_t plane = static_cast<size_t>(N) * N;
+  const size_t rplane = a.solo ? plane / 2 : plane;  // from one realization's rows to the next's
+  const int64_t in_stride = a.solo ? static_cast<int64_t>(rplane) : a.in_stride;
+  const size_t row_off = static_cast<size_t>(i0) * N;
+  const size_t ck_row = a.solo ? static_cast<size_t>(a.screen) * plane + static_cast<size_t>(r) * rplane + row_off
+                               : (static_cast<size_t>(r) * a.M + a.screen) * plane + row_off;
+  const size_t cw_row = a.ckpt_single ? static_cast<size_t>(r) * rplane + row_off : ck_row;
+  const bool want_ck = BWD && a.grad_screens && writes;
+
+  // every load of the block in flight before the twiddles are staged
+  float2 x[kE];
+  float2 wck[kE];
+  const float2* src = role == 0 ? a.scratch + j * plane + row_off : a.in + r * in_stride + row_off;
+#pragma unroll
+  for (int m = 0; m < kE; ++m) x[m] = (src + t)[T * m];
+  if constexpr (BWD) {
+    if (want_ck) {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) wck[m] = ld_s<true>(a.ckpt_in + cw_row + t + T * m);
+    }
+  }
+  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  if (role == 0) {
+    fft<N, kE, true, true>(x, lds, t, tw);
+    add_subharmonics<N>(a, j, i0, t, x);
+    float2* z = screen_row.strided(t);
+    if constexpr (RowLds::strided_ok<T>()) {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) z[m * RowLds::step<T>()] = x[m];
+    } else {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) screen_row[t + T * m] = x[m];
+    }
+  } else if (a.in_spectral) {
+    if (a.pre) {
+#pragma unroll
+      for (int m = 0; m < kE; ++m) {
+        const float2 h = (a.pre + t)[T * m];
+        x[m] = BWD ? c_mulc(x[m], h) : c_mul(x[m], h);
+      }
+    }
+    fft<N, kE, true, true>(x, lds, t, tw);
+  }
+  __syncthreads();  // the screen rows are in LDS
+  if (role == 0) return;
+  float2 z[kE];
+  float ph[kE];
+  lds_gather<T>(z, screen_row, t);
+#pragma unroll
+  for (int m = 0; m < kE; ++m) ph[m] = role == 1 ? z[m].x : z[m].y;
+  finish_row<N, BWD>(a, x, ph, wck, want_ck, writes, ck_row, cw_row,
+                     a.out + r * static_cast<int64_t>(rplane) + row_off, lds, t, tw);
+}
+
+template <int N, bool BWD>
+__global__ __launch_bounds__(trio_block<N>()) void row_trio_kernel(RowArgs a) { row_trio_body<N, BWD>(a); }
+
+// ---------------------------------------------------------------------------
 // Column pass: FFT along y, x h(k0)/N (x angular-spectrum correction), IFFT.
 // ---------------------------------------------------------------------------
 // Transfer-function modes of the column pass: Fresnel chirp only, or the
@@ -639,7 +737,9 @@ __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
   __shared__ float2 tw_lds[N];
   __shared__ float2 h_lds[N];
   TURPY_LDS_INIT(h_lds);
-  for (int i = threadIdx.x; i < N; i += blockDim.x) h_lds[i] = a.table[i];
+  // h, conjugated where the adjoint asks for it (the correction below is too)
+  const float sign = a.conj_table ? -1.0f : 1.0f;
+  for (int i = threadIdx.x; i < N; i += blockDim.x) h_lds[i] = make_float2(a.table[i].x, a.table[i].y * sign);
   const float2* chirp = h_lds;
   const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
   const float2* src = a.in + r * a.in_stride + k1;
@@ -651,8 +751,11 @@ __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
   for (int m = 0; m < kE; ++m) {
     const int k0 = t + T * m;
     float2 h = chirp[k0];
-    if constexpr (ANGULAR != TF_FRESNEL_ONLY) h = c_mul(h, angular_correction<ANGULAR>(a, k0, k1, N));
-    x[m] = a.conj_table ? c_mulc(x[m], h) : c_mul(x[m], h);
+    if constexpr (ANGULAR != TF_FRESNEL_ONLY) {
+      const float2 f = angular_correction<ANGULAR>(a, k0, k1, N);
+      h = c_mul(h, make_float2(f.x, f.y * sign));
+    }
+    x[m] = c_mul(x[m], h);
   }
   fft<N, kE, true, false, R2SEL>(x, lds, t, tw);
   float2* dst = a.out + r * static_cast<int64_t>(N) * N + k1;
@@ -1520,6 +1623,19 @@ bool solo_forward(const RowArgs& a) {
   return N > 1024 && a.R == 1 && !a.backward && !a.solo;
 }
 
+// The one-worker-per-transform schedule up to 2^20 pixels of scratch planes in a
+// launch, where its shorter chain beats the busier blocks of the others (us
+// with it and without, forward, events around each launch: n = 256, 32
+// realizations 16.6 / 19.6, 64 22.6 / 21.8; n = 512, 8 realizations 18.4 /
+// 21.7, 16 26.2 / 24.4; n = 1024, 2 realizations 20.7 / 22.1, 4 30.0 / 25.6;
+// the adjoint's lines lie at the same sizes or one step above).  The results
+// are the other schedules' bit for bit.
+template <int N>
+bool trio_pays(const RowArgs& a, int64_t planes) {
+  return trio_fits(N) && a.screen_mode == ROW_SCRATCH && !a.phase_out &&
+         planes * (a.solo ? N / 2 : N) * N <= (int64_t(1) << 20);
+}
+
 // The relay kernel for forward passes with synthesised screens and no
 // checkpoint output, where its workers are whole waves and it keeps three
 // waves per SIMD (N <= 1024); false: not launched.  With checkpoint writes
@@ -1572,7 +1688,13 @@ hipError_t row_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
   dim3 block(row_block<N>());
   if (a.screen_mode == ROW_NO_SCREEN)
     hipLaunchKernelGGL((row_pass_kernel<N, ROW_NO_SCREEN, false>), grid, block, 0, s, a);
-  else if (a.phase_out || (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(a)) {
+  else if (trio_pays<N>(a, pairs)) {
+    if constexpr (trio_fits(N)) {
+      const dim3 tgrid((a.solo ? N / 2 : N) / trio_rows<N>(), static_cast<uint32_t>(pairs)), tblock(trio_block<N>());
+      if (a.backward) hipLaunchKernelGGL((row_trio_kernel<N, true>), tgrid, tblock, 0, s, a);
+      else hipLaunchKernelGGL((row_trio_kernel<N, false>), tgrid, tblock, 0, s, a);
+    }
+  } else if (a.phase_out || (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(a)) {
     // screen output, grids too small for the two halves to sit in separate
     // waves, or a single realization on the pair schedule
     if (a.screen_mode == ROW_SCRATCH && !a.backward)
@@ -1745,6 +1867,11 @@ void row_pair_group_kernel(const RowArgs* tab, GroupCall g) {
   row_pair_body<N, ROW_SCRATCH, false>(row_record(tab, blockIdx.z, g));
 }
 
+template <int N, bool BWD>
+__global__ __launch_bounds__(trio_block<N>()) void row_trio_group_kernel(const RowArgs* tab, GroupCall g) {
+  row_trio_body<N, BWD>(BWD ? row_record_bwd(tab, blockIdx.z, g) : row_record(tab, blockIdx.z, g));
+}
+
 template <int N>
 __global__ __launch_bounds__(relay_block<N>()) __attribute__((amdgpu_waves_per_eu(kRowWaves, 0)))
 void row_relay_group_kernel(const RowArgs* tab, GroupCall g) {
@@ -1797,6 +1924,12 @@ hipError_t row_group_launch(const RowArgs& proto, const RowArgs* tab, uint32_t c
                        s, tab, g);
   } else if (proto.screen_mode != ROW_SCRATCH) {
     return hipErrorInvalidValue;
+  } else if (trio_pays<N>(proto, pairs * count)) {
+    if constexpr (trio_fits(N)) {
+      const dim3 grid(rows / trio_rows<N>(), P, count), block(trio_block<N>());
+      if (proto.backward) hipLaunchKernelGGL((row_trio_group_kernel<N, true>), grid, block, 0, s, tab, g);
+      else hipLaunchKernelGGL((row_trio_group_kernel<N, false>), grid, block, 0, s, tab, g);
+    }
   } else if (proto.backward) {
     if (small)
       hipLaunchKernelGGL((row_pass_group_bwd_kernel<N>), dim3(N / G, P, count), dim3(row_block<N>()), 0, s, tab, g);

@@ -80,6 +80,14 @@ constexpr int pair_rows() {
 template <int N>
 constexpr int pair_block() { return 2 * pair_rows<N>() * (N / kE); }
 
+// Row pass with one worker per transform: a worker is one wave over
+// `trio_rows` rows.
+constexpr bool trio_fits(int n) { return n >= 64 && n <= 1024; }
+template <int N>
+constexpr int trio_rows() { return 64 / (N / kE); }
+template <int N>
+constexpr int trio_block() { return 3 * trio_rows<N>() * (N / kE); }
+
 // Relay row pass: two workers of `relay_rows` rows each per block, over two
 // row groups (2 relay_rows <= N).  Used where a worker is whole waves.
 template <int N>

@@ -52,6 +52,9 @@ def family(kernel_name):
         if m.group(2) == "0":
             return "row_plain"
         return "row_bwd" if m.group(3) == "true" else "row_fwd"
+    m = re.search(r"row_trio_(?:group_)?kernel<(\d+), (true|false)>", n)
+    if m:
+        return "row_bwd" if m.group(2) == "true" else "row_fwd"
     m = re.search(r"row_pass_group_kernel<(\d+), (\d+)>", n)
     if m:
         return "row_plain" if m.group(2) == "0" else "row_fwd"
