@@ -1328,9 +1328,9 @@ __global__ __launch_bounds__(1024) void finalize_kernel(FinalizeArgs a) {
 
 // ---------------------------------------------------------------------------
 // The same statistics over many blocks.  One block reads the moments with one
-// CU (a full pass over 1024 x 1024 sums takes it about 0.35 ms, the bisection
-// 31 such passes: 13.5 ms in all); spread over the chip every pass is a few
-// microseconds, bound by launch latency.  Partial sums need memory that a
+// CU (a full pass over 1024 x 1024 sums takes it about 0.4 ms, the bisection
+// 31 such passes: 14.6 ms in all); spread over the chip a pass is 5 to 10 us,
+// bound by launch latency and FP64 arithmetic, and all of them 0.10 ms.  Partial sums need memory that a
 // caller's 8-word summary does not have, so the SI map, written last, holds
 // them until then.  The sums are FP64 in a fixed order (thread, wave, block),
 // the same bits on every run; S(t), the power above a threshold, is added up
@@ -1342,23 +1342,27 @@ __global__ __launch_bounds__(1024) void finalize_kernel(FinalizeArgs a) {
 //   finalize_summary  the 8 results
 //   finalize_map      the SI map, over the scratch
 // ---------------------------------------------------------------------------
-constexpr int kFinThreads = 1024;
+// Up to 256 blocks of 8 waves: every block adds up the sums of all blocks
+// before it starts, and joining 15 sums over a wave takes 90 steps, so more
+// blocks or waves cost more than they read faster (all passes at n = 1024,
+// 0.999 of the power: 104 us; 127 with 128 blocks; 182 with 512 of 4 waves
+// joined by lane exchanges through LDS).
+constexpr int kFinThreads = 512;
 constexpr int kFinWaves = kFinThreads / 64;
 constexpr int kFinSplit = 16;    // pieces a pass splits the bracket into
 constexpr int kFinPasses = 8;    // 16^8 > 0x7F800000
 constexpr int kFinMaxBlocks = 256;
-static_assert(kFinSplit - 1 <= kFinWaves && 8 <= kFinWaves, "a wave joins each sum");
 
-// Blocks for np pixels, four per thread until every CU has a block.
+// Blocks for np pixels: eight pixels a thread until every CU has its blocks.
 constexpr int finalize_blocks(int64_t np) {
-  return np / (4 * kFinThreads) < 1 ? 1
-                                    : (np / (4 * kFinThreads) > kFinMaxBlocks ? kFinMaxBlocks
-                                                                              : static_cast<int>(np / (4 * kFinThreads)));
+  const int64_t b = np / (8 * kFinThreads);
+  return b < 1 ? 1 : (b > kFinMaxBlocks ? kFinMaxBlocks : static_cast<int>(b));
 }
 
 // The scratch (doubles): per-block sums of the first pass [4][nb], of the
 // region [7][nb], of two alternating bracket passes [2][16][nb], and the
-// bracket each pass starts from [passes + 1][2].
+// bracket each pass starts from [passes + 1][2], with the power the region has
+// to hold after them.
 struct FinScratch {
   double *first, *region, *split, *bracket;
   int nb;
@@ -1367,7 +1371,27 @@ __host__ __device__ inline FinScratch finalize_scratch(double* base, int nb) {
   return FinScratch{base, base + 4 * nb, base + 11 * nb, base + (11 + 2 * kFinSplit) * nb, nb};
 }
 constexpr int64_t finalize_scratch_bytes(int nb) {
-  return static_cast<int64_t>(sizeof(double)) * ((11 + 2 * kFinSplit) * nb + 2 * (kFinPasses + 1));
+  return static_cast<int64_t>(sizeof(double)) * ((11 + 2 * kFinSplit) * nb + 2 * (kFinPasses + 1) + 1);
+}
+
+// v joined over the wave, in lane 63: data-parallel moves inside each row of 16
+// lanes, then the rows' last lanes passed on (lanes without a source take 0,
+// which neither a sum nor a maximum of non-negative values notices).
+template <int CTRL, int ROWS, class Op>
+__device__ __forceinline__ double finalize_step(int c, double v, Op op) {
+  const int64_t b = __builtin_bit_cast(int64_t, v);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, ROWS, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, ROWS, 0xF, true);
+  return op(c, v, __builtin_bit_cast(double, static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo)));
+}
+template <class Op>
+__device__ __forceinline__ double finalize_wave(int c, double v, Op op) {
+  v = finalize_step<0x111, 0xF>(c, v, op);  // row_shr:1
+  v = finalize_step<0x112, 0xF>(c, v, op);  // row_shr:2
+  v = finalize_step<0x114, 0xF>(c, v, op);  // row_shr:4
+  v = finalize_step<0x118, 0xF>(c, v, op);  // row_shr:8
+  v = finalize_step<0x142, 0xA>(c, v, op);  // row_bcast:15 into rows 1 and 3
+  return finalize_step<0x143, 0xC>(c, v, op);  // row_bcast:31 into rows 2 and 3
 }
 
 // Join v[0..C) over the block into out[c * nb + block]; in wave, then wave order.
@@ -1376,10 +1400,8 @@ __device__ __forceinline__ void finalize_join(double (&v)[C], double* out, int n
                                               Op op) {
   const int wave = threadIdx.x / 64;
 #pragma unroll
-  for (int c = 0; c < C; ++c)
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v[c] = op(c, v[c], __shfl_xor(v[c], off));
-  if (threadIdx.x % 64 == 0) {
+  for (int c = 0; c < C; ++c) v[c] = finalize_wave(c, v[c], op);
+  if (threadIdx.x % 64 == 63) {
 #pragma unroll
     for (int c = 0; c < C; ++c) red[wave * kFinSplit + c] = v[c];
   }
@@ -1392,17 +1414,17 @@ __device__ __forceinline__ void finalize_join(double (&v)[C], double* out, int n
   }
 }
 
-// Join the blocks' values of `count` quantities (one wave each) into tot[]; every block
-// gets the same bits.  Block-wide barrier at the end.
+// Join the blocks' values of `count` quantities into tot[] (a wave takes one at a
+// time); every block gets the same bits.  Block-wide barrier at the end.
 template <class Op>
 __device__ __forceinline__ void finalize_totals(const double* part, int nb, int count, double* tot, Op op) {
-  const int c = threadIdx.x / 64, lane = threadIdx.x % 64;
-  if (c < count) {
+  const int lane = threadIdx.x % 64;
+  for (int c = threadIdx.x / 64; c < count; c += kFinWaves) {
     const double* p = part + static_cast<size_t>(c) * nb;
     double s = lane < nb ? p[lane] : 0.0;
     for (int i = lane + 64; i < nb; i += 64) s = op(c, s, p[i]);
-    for (int off = 32; off > 0; off >>= 1) s = op(c, s, __shfl_xor(s, off));
-    if (lane == 0) tot[c] = s;
+    s = finalize_wave(c, s, op);
+    if (lane == 63) tot[c] = s;
   }
   __syncthreads();
 }
@@ -1438,15 +1460,16 @@ __global__ __launch_bounds__(kFinThreads) void finalize_sums_kernel(FinalizeArgs
 // S(lo) >= target, from pass q - 1's bracket and sums.  Same bits in every block.
 __device__ __forceinline__ void finalize_bracket(const FinalizeArgs& a, const FinScratch& w, int q, double* tot,
                                                  uint32_t* lo, uint32_t* hi) {
-  __shared__ double first[4];
-  TURPY_LDS_INIT(first);
-  finalize_totals(w.first, w.nb, 4, first, FinFirst());
   *lo = 0;
   *hi = 0x7F800000u;  // +inf, above every finite m1
-  if (q == 0) return;
+  if (q == 0) {
+    finalize_totals(w.first + 2 * static_cast<size_t>(w.nb), w.nb, 1, tot, FinAdd());
+    if (blockIdx.x == 0 && threadIdx.x == 0) w.bracket[2 * (kFinPasses + 1)] = a.power_fraction * tot[0];
+    return;
+  }
   *lo = static_cast<uint32_t>(w.bracket[2 * (q - 1)]);
   *hi = static_cast<uint32_t>(w.bracket[2 * (q - 1) + 1]);
-  const double target = a.power_fraction * first[2];
+  const double target = w.bracket[2 * (kFinPasses + 1)];
   finalize_totals(w.split + static_cast<size_t>((q - 1) % 2) * kFinSplit * w.nb, w.nb, kFinSplit - 1, tot, FinAdd());
   const uint32_t step = (*hi - *lo + kFinSplit - 1) / kFinSplit;
   const uint32_t lo0 = *lo, hi0 = *hi;
@@ -1478,12 +1501,20 @@ __global__ __launch_bounds__(kFinThreads) void finalize_bracket_kernel(FinalizeA
   double v[kFinSplit - 1];
 #pragma unroll
   for (int j = 0; j < kFinSplit - 1; ++j) v[j] = 0;
-  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kFinThreads + threadIdx.x; p < np;
-       p += static_cast<int64_t>(w.nb) * kFinThreads) {
-    const float m = mean_intensity(a, p, np);
+  const int64_t stride = static_cast<int64_t>(w.nb) * kFinThreads;
+  constexpr int U = 8;  // pixels whose loads are in flight together
+  for (int64_t p0 = static_cast<int64_t>(blockIdx.x) * kFinThreads + threadIdx.x; p0 < np; p0 += U * stride) {
+    float m[U];
 #pragma unroll
-    for (int j = 0; j < kFinSplit - 1; ++j)
-      if (m >= __uint_as_float(lo + static_cast<uint32_t>(j + 1) * step)) v[j] += m;
+    for (int u = 0; u < U; ++u) {
+      const int64_t p = p0 + u * stride;
+      m[u] = p < np ? mean_intensity(a, p, np) : -1.0f;  // below every threshold
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int j = 0; j < kFinSplit - 1; ++j)
+        if (m[u] >= __uint_as_float(lo + static_cast<uint32_t>(j + 1) * step)) v[j] += m[u];
   }
   finalize_join(v, w.split + static_cast<size_t>(q % 2) * kFinSplit * w.nb, w.nb, red, FinAdd());
 }
