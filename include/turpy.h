@@ -353,6 +353,23 @@ turpy_status turpy_receiver_backward(int32_t n, double dx, double aperture_diame
                                      const void* grad_out, void* grad_u, float* grad_theta1,
                                      float* grad_theta2, void* ws, size_t ws_bytes, void* stream);
 
+/* The loss the receiver's masks are trained on (Sec. 2.5, Sec. 4) over received
+ * fields u complex64 [batch][pixels], I = |u|^2, m1 and var its mean and
+ * population variance over the batch, A the aperture, V the vacuum intensity
+ * (float [pixels] each):
+ *   loss = sum A var / sum A m1^2 + sum (m1 - V)^2 / sum V^2.
+ * Outputs (device): mean float [pixels] = m1; sums double[4 + 4 * 1024], the
+ * first four being those sums in order, the rest scratch; loss float[1].  The
+ * sums are FP64 in a fixed order (bitwise reproducible).  The adjoint takes
+ * mean and sums as the forward call left them and grad_loss float[1] and writes
+ * grad_u complex64 [batch][pixels].  1 <= pixels <= 2^32, 1 <= batch <= 2^19;
+ * errors: INVALID. */
+turpy_status turpy_receiver_loss(int64_t pixels, int64_t batch, const void* u, const float* i_vac,
+                                 const float* aperture, float* mean, double* sums, float* loss, void* stream);
+turpy_status turpy_receiver_loss_backward(int64_t pixels, int64_t batch, const void* u, const float* i_vac,
+                                          const float* aperture, const float* mean, const double* sums,
+                                          const float* grad_loss, void* grad_u, void* stream);
+
 /* ---------------------------------------------------------------------------
  * Uneven batches: many path instances, each with its own grid size, screen
  * count, wavelength and distances, propagated by one call on the caller's
@@ -559,7 +576,7 @@ turpy_status turpy_batch_tune(turpy_batch* batch, uint32_t flags, void* ws, size
  * on that kernel's stream; turpy_profile(0) stops recording.  Kernel families:
  * "row_fwd", "row_bwd", "row_plain", "row_moments", "col", "synth", "sh", "evolve",
  * "stats", "finalize", "copy", "sum", "noise", "nonfinite", "recv_row", "recv_col",
- * "recv_col_grad", "recv_row_grad", "recv_reduce".  turpy_profile_read waits for the recorded events and
+ * "recv_col_grad", "recv_row_grad", "recv_reduce", "loss".  turpy_profile_read waits for the recorded events and
  * returns the launch count and summed duration (ms) of one family (zero when it
  * never ran).  turpy_profile_only(family) restricts the bracketing to one
  * family (the others launch with no events around them, so that timing one

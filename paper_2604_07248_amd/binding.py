@@ -36,7 +36,8 @@ EXPORTS = [
     "turpy_batch_propagate", "turpy_batch_propagate_backward", "turpy_plan_tune", "turpy_plan_widths",
     "turpy_plan_set_widths", "turpy_tune_cache_get", "turpy_tune_cache_put", "turpy_tune_cache_clear",
     "turpy_batch_tune", "turpy_plan_config", "turpy_plan_set_config", "turpy_receiver_setup", "turpy_noise", "turpy_propagate_static", "turpy_checkpoint_size", "turpy_evolve_propagate",
-    "turpy_plan_bind_moments", "turpy_debug_fail_launch", "turpy_batch_group_limit",
+    "turpy_plan_bind_moments", "turpy_debug_fail_launch", "turpy_batch_group_limit", "turpy_receiver_loss",
+    "turpy_receiver_loss_backward",
 ]
 
 
@@ -127,6 +128,8 @@ def lib():
                                      c_void_p, c_size_t, c_void_p]
         L.turpy_receiver_backward.argtypes = [c_int32, c_double, c_double, c_int64, c_void_p, c_void_p, c_void_p,
                                               c_void_p, c_void_p, c_void_p, c_void_p, c_void_p, c_size_t, c_void_p]
+        L.turpy_receiver_loss.argtypes = [c_int64, c_int64] + [c_void_p] * 7
+        L.turpy_receiver_loss_backward.argtypes = [c_int64, c_int64] + [c_void_p] * 8
         L.turpy_profile.argtypes = [c_int32]
         L.turpy_profile_only.argtypes = [c_char_p]
         L.turpy_profile_read.argtypes = [c_char_p, POINTER(c_int64), POINTER(c_double)]
@@ -324,6 +327,17 @@ def receiver_backward(n, dx, diameter, batch, u_ptr, th1_ptr, th2_ptr, gout_ptr,
                       ws_bytes, stream):
     check(lib().turpy_receiver_backward(n, dx, diameter, batch, u_ptr, th1_ptr, th2_ptr, gout_ptr, gu_ptr, g1_ptr,
                                         g2_ptr, ws_ptr, ws_bytes, stream))
+
+
+def receiver_loss(pixels, batch, u_ptr, i_vac_ptr, aperture_ptr, mean_ptr, sums_ptr, loss_ptr, stream):
+    check(lib().turpy_receiver_loss(pixels, batch, u_ptr, i_vac_ptr, aperture_ptr, mean_ptr, sums_ptr, loss_ptr,
+                                    stream))
+
+
+def receiver_loss_backward(pixels, batch, u_ptr, i_vac_ptr, aperture_ptr, mean_ptr, sums_ptr, gloss_ptr, gu_ptr,
+                           stream):
+    check(lib().turpy_receiver_loss_backward(pixels, batch, u_ptr, i_vac_ptr, aperture_ptr, mean_ptr, sums_ptr,
+                                             gloss_ptr, gu_ptr, stream))
 
 
 def profile(enable):

@@ -1191,6 +1191,52 @@ turpy_status turpy_receiver_backward(int32_t n, double dx, double aperture_diame
   return TURPY_OK;
 }
 
+static turpy_status check_loss(int64_t pixels, int64_t batch) {
+  if (pixels < 1 || pixels > (int64_t(1) << 32)) return fail(TURPY_E_INVALID, "receiver_loss: pixels out of range");
+  // the adjoint's grid holds 65535 chunks of 16 realizations
+  if (batch < 1 || batch > (int64_t(1) << 19)) return fail(TURPY_E_INVALID, "receiver_loss: batch out of range");
+  return TURPY_OK;
+}
+
+turpy_status turpy_receiver_loss(int64_t pixels, int64_t batch, const void* u, const float* i_vac,
+                                 const float* aperture, float* mean, double* sums, float* loss, void* stream) {
+  if (turpy_status st = check_loss(pixels, batch)) return st;
+  if (!u || !i_vac || !aperture || !mean || !sums || !loss) return fail(TURPY_E_INVALID, "receiver_loss: NULL argument");
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  LossArgs a{};
+  a.u = static_cast<const float2*>(u);
+  a.batch = batch;
+  a.pixels = pixels;
+  a.i_vac = i_vac;
+  a.aperture = aperture;
+  a.mean = mean;
+  a.sums = sums;
+  a.loss = loss;
+  TURPY_HIP(timed("loss", st, [&] { return launch_loss(a, st); }), "receiver_loss");
+  return TURPY_OK;
+}
+
+turpy_status turpy_receiver_loss_backward(int64_t pixels, int64_t batch, const void* u, const float* i_vac,
+                                          const float* aperture, const float* mean, const double* sums,
+                                          const float* grad_loss, void* grad_u, void* stream) {
+  if (turpy_status st = check_loss(pixels, batch)) return st;
+  if (!u || !i_vac || !aperture || !mean || !sums || !grad_loss || !grad_u)
+    return fail(TURPY_E_INVALID, "receiver_loss_backward: NULL argument");
+  hipStream_t st = static_cast<hipStream_t>(stream);
+  LossArgs a{};
+  a.u = static_cast<const float2*>(u);
+  a.batch = batch;
+  a.pixels = pixels;
+  a.i_vac = i_vac;
+  a.aperture = aperture;
+  a.mean = const_cast<float*>(mean);
+  a.sums = const_cast<double*>(sums);
+  a.grad_loss = grad_loss;
+  a.grad_u = static_cast<float2*>(grad_u);
+  TURPY_HIP(timed("loss", st, [&] { return launch_loss_grad(a, st); }), "receiver_loss_backward");
+  return TURPY_OK;
+}
+
 }  // extern "C"
 
 // ---------------------------------------------------------------------------

@@ -197,6 +197,20 @@ struct RecvArgs {
   int conj_mask;            // use exp(-i theta2)
 };
 
+// The receiver's training loss over fields [batch][pixels].
+constexpr int kLossBlocks = 1024;  // partial sums of the loss, at most
+struct LossArgs {
+  const float2* u;          // [batch][pixels]
+  int64_t batch, pixels;
+  const float* i_vac;       // [pixels] target intensity
+  const float* aperture;    // [pixels] weights of the scintillation term
+  float* mean;              // [pixels] mean intensity
+  double* sums;             // [4]: sum A var, sum A m1^2, sum (m1 - i_vac)^2, sum i_vac^2; then [blocks][4] partials
+  float* loss;
+  const float* grad_loss;   // adjoint: dL/dloss
+  float2* grad_u;           // adjoint: [batch][pixels]
+};
+
 hipError_t launch_row(int n, const RowArgs& a, int64_t pairs, hipStream_t s);
 // Grouped launches over `count` instances (records in device memory, `proto`
 // one of them as built on the host, for the kernel choice).  The row passes
@@ -230,6 +244,8 @@ hipError_t launch_recv_col(const RecvArgs& a, hipStream_t s);        // FFT_y, x
 hipError_t launch_recv_col_grad(const RecvArgs& a, hipStream_t s);   // th2 gradient partials + gradient path
 hipError_t launch_recv_row_grad(const RecvArgs& a, hipStream_t s);   // th1 gradient partials + grad u
 hipError_t launch_recv_reduce(const RecvArgs& a, float* grad, int centre_shift, hipStream_t s);
+hipError_t launch_loss(const LossArgs& a, hipStream_t s);
+hipError_t launch_loss_grad(const LossArgs& a, hipStream_t s);
 hipError_t launch_noise(const NoiseArgs& a, hipStream_t s);
 // out[p] = sum over r < R of in[r * count + p] (in order, compensated)
 hipError_t launch_sum_planes(const float2* in, int64_t R, int64_t count, float2* out, hipStream_t s);

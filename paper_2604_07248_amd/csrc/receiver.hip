@@ -217,6 +217,113 @@ __global__ __launch_bounds__(256) void recv_reduce_kernel(const float* partial, 
   grad[q] = s;
 }
 
+// ---------------------------------------------------------------------------
+// The training loss (scintillation inside the aperture plus the distance of
+// the mean intensity from the vacuum beam's) and its gradient.  Forward: one
+// read of the fields; each thread adds its pixel's I and I^2 over the batch in
+// FP64, which holds the variance of weak fluctuations without a second pass,
+// and the four sums over the pixels join in a fixed order.  Adjoint: one read
+// and one write of the fields.  Both are bound by that traffic (64 fields of
+// 512 x 512, forward and gradient: about 0.09 ms; as some forty elementwise
+// and reduction kernels of an array library 0.80 ms).
+// ---------------------------------------------------------------------------
+constexpr int kLossThreads = 256;
+
+template <int C>
+__device__ __forceinline__ void loss_join(double (&v)[C], double* out) {
+  __shared__ double red[C * (kLossThreads / 64)];
+  TURPY_LDS_INIT(red);
+  const int wave = threadIdx.x / 64;
+#pragma unroll
+  for (int c = 0; c < C; ++c)
+    for (int off = 32; off > 0; off >>= 1) v[c] += __shfl_xor(v[c], off);
+  if (threadIdx.x % 64 == 0)
+    for (int c = 0; c < C; ++c) red[wave * C + c] = v[c];
+  __syncthreads();
+  if (threadIdx.x < C) {
+    double s = 0;
+    for (int w = 0; w < kLossThreads / 64; ++w) s += red[w * C + threadIdx.x];
+    out[threadIdx.x] = s;
+  }
+}
+
+__global__ __launch_bounds__(kLossThreads) void loss_kernel(LossArgs a) {
+  double v[4] = {0, 0, 0, 0};
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kLossThreads;
+  const double inv = 1.0 / static_cast<double>(a.batch);
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kLossThreads + threadIdx.x; p < a.pixels; p += stride) {
+    double s1 = 0, s2 = 0;
+    auto add = [&](float2 u) {
+      const double i = static_cast<double>(u.x * u.x + u.y * u.y);
+      s1 += i;
+      s2 += i * i;
+    };
+    constexpr int U = 16;  // loads in flight per thread
+    int64_t b = 0;
+    for (; b + U <= a.batch; b += U) {
+      float2 u[U];
+#pragma unroll
+      for (int q = 0; q < U; ++q) u[q] = ld_s<true>(a.u + (b + q) * a.pixels + p);
+#pragma unroll
+      for (int q = 0; q < U; ++q) add(u[q]);
+    }
+    for (; b < a.batch; ++b) add(ld_s<true>(a.u + b * a.pixels + p));
+    const double m1 = s1 * inv;
+    const double var = a.batch == 1 ? m1 - m1 : fmax(s2 * inv - m1 * m1, 0.0) + (s2 - s2);
+    const double ap = a.aperture[p], iv = a.i_vac[p];
+    a.mean[p] = static_cast<float>(m1);
+    v[0] += ap * var;
+    v[1] += ap * m1 * m1;
+    v[2] += (m1 - iv) * (m1 - iv);
+    v[3] += iv * iv;
+  }
+  loss_join<4>(v, a.sums + 4 + 4 * static_cast<size_t>(blockIdx.x));
+}
+
+__global__ __launch_bounds__(kLossThreads) void loss_total_kernel(LossArgs a, int blocks) {
+  double v[4] = {0, 0, 0, 0};
+  for (int b = threadIdx.x; b < blocks; b += kLossThreads)
+#pragma unroll
+    for (int c = 0; c < 4; ++c) v[c] += a.sums[4 + 4 * static_cast<size_t>(b) + c];
+  loss_join<4>(v, a.sums);
+  __syncthreads();
+  if (threadIdx.x == 0) *a.loss = static_cast<float>(a.sums[0] / a.sums[1] + a.sums[2] / a.sums[3]);
+}
+
+// Realizations a thread of the adjoint takes.
+constexpr int kLossChunk = 16;
+
+// dL/dI_b = (2 A / (B S1)) (I_b - m1) + (1/B) (-2 S0 A m1 / S1^2 + 2 (m1 - i_vac) / S3)
+// with S0..S3 the four sums (the mean's share of the variance's derivative is
+// zero), and dL/du = 2 u dL/dI.
+__global__ __launch_bounds__(kLossThreads) void loss_grad_kernel(LossArgs a) {
+  const int64_t p = static_cast<int64_t>(blockIdx.x) * kLossThreads + threadIdx.x;
+  if (p >= a.pixels) return;
+  const double inv = 1.0 / static_cast<double>(a.batch), g = 2.0 * *a.grad_loss;
+  const double s0 = a.sums[0], s1 = a.sums[1], s3 = a.sums[3];
+  const double m1 = a.mean[p], ap = a.aperture[p], iv = a.i_vac[p];
+  const float mean = a.mean[p];
+  const float slope = static_cast<float>(g * 2.0 * ap * inv / s1);
+  const float level = static_cast<float>(g * inv * (-2.0 * s0 * ap * m1 / (s1 * s1) + 2.0 * (m1 - iv) / s3));
+  const int64_t b0 = static_cast<int64_t>(blockIdx.y) * kLossChunk;
+  if (b0 + kLossChunk <= a.batch) {
+    float2 u[kLossChunk];
+#pragma unroll
+    for (int q = 0; q < kLossChunk; ++q) u[q] = ld_s<true>(a.u + (b0 + q) * a.pixels + p);
+#pragma unroll
+    for (int q = 0; q < kLossChunk; ++q) {
+      const float w = slope * (u[q].x * u[q].x + u[q].y * u[q].y - mean) + level;
+      a.grad_u[(b0 + q) * a.pixels + p] = c_scale(u[q], w);
+    }
+  } else {
+    for (int64_t b = b0; b < a.batch; ++b) {
+      const float2 u = a.u[b * a.pixels + p];
+      const float w = slope * (u.x * u.x + u.y * u.y - mean) + level;
+      a.grad_u[b * a.pixels + p] = c_scale(u, w);
+    }
+  }
+}
+
 template <int N>
 hipError_t row_in_launch(const RecvArgs& a, hipStream_t s) {
   hipLaunchKernelGGL(recv_row_in_kernel<N>, dim3(N / row_groups<N>(), static_cast<uint32_t>(a.batch)),
@@ -265,6 +372,21 @@ hipError_t launch_recv_reduce(const RecvArgs& a, float* grad, int centre_shift, 
   const int64_t np = static_cast<int64_t>(a.n) * a.n;
   hipLaunchKernelGGL(recv_reduce_kernel, dim3(static_cast<uint32_t>((np + 255) / 256)), dim3(256), 0, s, a.partial,
                      a.chunks, a.n, grad, centre_shift);
+  return hipGetLastError();
+}
+
+hipError_t launch_loss(const LossArgs& a, hipStream_t s) {
+  const int64_t want = (a.pixels + kLossThreads - 1) / kLossThreads;
+  const int blocks = static_cast<int>(want < kLossBlocks ? want : kLossBlocks);
+  hipLaunchKernelGGL(loss_kernel, dim3(static_cast<uint32_t>(blocks)), dim3(kLossThreads), 0, s, a);
+  hipLaunchKernelGGL(loss_total_kernel, dim3(1), dim3(kLossThreads), 0, s, a, blocks);
+  return hipGetLastError();
+}
+
+hipError_t launch_loss_grad(const LossArgs& a, hipStream_t s) {
+  const dim3 grid(static_cast<uint32_t>((a.pixels + kLossThreads - 1) / kLossThreads),
+                  static_cast<uint32_t>((a.batch + kLossChunk - 1) / kLossChunk));
+  hipLaunchKernelGGL(loss_grad_kernel, grid, dim3(kLossThreads), 0, s, a);
   return hipGetLastError();
 }
 

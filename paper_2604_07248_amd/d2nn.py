@@ -8,17 +8,74 @@ intensity to the vacuum beam through the same receiver:
     L = sum_A Var_b(I) / sum_A (E_b I)^2 + sum (E_b I - I_vac)^2 / sum I_vac^2
 
 with Adam and a one-cycle learning-rate schedule from a constant (zero) phase
-initialisation (Sec. 2.5).  The loss is a handful of reductions over |U|^2 in
-PyTorch; propagation and receiver (forward and adjoint) run in libturpy.
+initialisation (Sec. 2.5).  Propagation, receiver and loss (forward and adjoint) run in
+libturpy.
 """
 
 import numpy as np
 import torch
 
 from . import api
+from . import binding as B
+
+
+class _Loss(torch.autograd.Function):
+    """The loss and its gradient in two passes over the fields
+    (turpy_receiver_loss)."""
+
+    SUMS = 4 + 4 * 1024
+
+    @staticmethod
+    def forward(ctx, u_out, i_vac, aperture):
+        pixels, batch = i_vac.numel(), u_out.shape[0]
+        mean = torch.empty_like(i_vac)
+        sums = torch.empty(_Loss.SUMS, dtype=torch.float64, device=u_out.device)
+        loss = torch.empty((), dtype=torch.float32, device=u_out.device)
+        B.receiver_loss(pixels, batch, api._ptr(u_out), api._ptr(i_vac), api._ptr(aperture), api._ptr(mean),
+                        api._ptr(sums), api._ptr(loss), api._stream())
+        ctx.save_for_backward(u_out, i_vac, aperture, mean, sums)
+        return loss
+
+    @staticmethod
+    def backward(ctx, grad_loss):
+        u_out, i_vac, aperture, mean, sums = ctx.saved_tensors
+        if torch.is_grad_enabled():  # create_graph: a gradient that can be differentiated again
+            return torch.autograd.grad(_loss_ops(u_out, i_vac, aperture), u_out, grad_loss, create_graph=True) + \
+                (None, None)
+        grad_u = torch.empty_like(u_out)
+        B.receiver_loss_backward(i_vac.numel(), u_out.shape[0], api._ptr(u_out), api._ptr(i_vac), api._ptr(aperture),
+                                 api._ptr(mean), api._ptr(sums), api._ptr(grad_loss.resolve_neg()), api._ptr(grad_u),
+                                 api._stream())
+        return grad_u, None, None
+
+
+def _fused(u_out, i_vac, aperture):
+    """Whether the library's kernels can stand in for the tensor operations:
+    contiguous complex64 fields and float32 planes on the current GPU, no
+    gradient asked for the planes, and nobody watching the operations (function
+    transforms, forward-mode derivatives, tracing, compilation, tensor subclasses)."""
+    planes = (i_vac, aperture)
+    if any(type(t) not in (torch.Tensor, torch.nn.Parameter) for t in (u_out,) + planes):
+        return False
+    if torch._C._are_functorch_transforms_active() or torch.jit.is_tracing() or torch.compiler.is_compiling():
+        return False
+    if torch.autograd.forward_ad.unpack_dual(u_out).tangent is not None:
+        return False
+    if torch.overrides._get_current_function_mode_stack() or torch.utils._python_dispatch._get_current_dispatch_mode():
+        return False
+    return (u_out.is_cuda and u_out.device.index == torch.cuda.current_device() and u_out.dtype == torch.complex64
+            and u_out.dim() == 3 and u_out.is_contiguous() and not u_out.is_conj() and 0 < u_out.numel()
+            and u_out.shape[0] <= 1 << 19
+            and all(t.device == u_out.device and t.dtype == torch.float32 and t.shape == u_out.shape[1:]
+                    and t.is_contiguous() and not t.is_neg() and not t.requires_grad
+                    and torch.autograd.forward_ad.unpack_dual(t).tangent is None for t in planes))
 
 
 def loss_fn(u_out, i_vac, aperture):
+    return (_Loss.apply if _fused(u_out, i_vac, aperture) else _loss_ops)(u_out, i_vac, aperture)
+
+
+def _loss_ops(u_out, i_vac, aperture):
     inten = u_out.real ** 2 + u_out.imag ** 2
     m1 = inten.mean(0)
     var = ((inten - m1) ** 2).mean(0)

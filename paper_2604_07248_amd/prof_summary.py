@@ -67,7 +67,8 @@ def family(kernel_name):
                      ("stats_kernel", "stats"), ("finalize_", "finalize"), ("copy_kernel", "copy"),
                      ("sum_planes_kernel", "sum"), ("noise_kernel", "noise"), ("nonfinite_kernel", "nonfinite"),
                      ("recv_row_in", "recv_row"), ("recv_col_grad", "recv_col_grad"), ("recv_col", "recv_col"),
-                     ("recv_row_grad", "recv_row_grad"), ("recv_reduce", "recv_reduce")):
+                     ("recv_row_grad", "recv_row_grad"), ("recv_reduce", "recv_reduce"),
+                     ("loss_", "loss")):
         if key in n:
             return fam
     return None
