@@ -579,7 +579,11 @@ class Propagate(torch.autograd.Function):
     @staticmethod
     def forward(ctx, u_in, screens, plan, seed, t, reversible=False):
         scr = screens.contiguous() if screens is not None else None
-        if reversible:
+        if not (ctx.needs_input_grad[0] or ctx.needs_input_grad[1]):
+            # nothing to differentiate (training optics behind the path): no backward
+            # follows, and no checkpoints are written for it
+            u_out = plan.propagate(u_in.contiguous(), seed, t, screens=scr)
+        elif reversible:
             u_out = plan.propagate(u_in.contiguous(), seed, t, screens=scr)
             ctx.save_for_backward(u_out, screens)
         else:
