@@ -147,9 +147,9 @@ turpy_status turpy_plan_create(turpy_plan** out, const turpy_path* p, uint32_t f
   }
 
   // FP64-generated tables
-  std::vector<float2> tw(n), row(static_cast<size_t>(M + 1) * n), col(static_cast<size_t>(M + 1) * n),
+  const std::vector<float2> tw = twiddle_tables(n);
+  std::vector<float2> row(static_cast<size_t>(M + 1) * n), col(static_cast<size_t>(M + 1) * n),
       shp(static_cast<size_t>(3) * n);
-  for (int i = 0; i < n; ++i) tw[i] = phasor(-static_cast<double>(i) / n);
   for (int s = 0; s <= M; ++s) {
     // h(k) = exp(-i pi (lambda/n0) dz f_k^2): revolutions -(lambda/n0) dz df^2 k^2 / 2
     const double a = (p->wavelength / p->n0) * pl->dz[s] * df * df * 0.5;
@@ -1074,11 +1074,10 @@ turpy_status turpy_receiver_setup(int32_t n) {
   TURPY_HIP(hipGetDevice(&dev), "receiver_setup");
   std::lock_guard<std::mutex> lock(g_tw_mutex);
   if (g_tw_cache.count({dev, n})) return TURPY_OK;
-  std::vector<float2> tw(n);
-  for (int i = 0; i < n; ++i) tw[i] = phasor(-static_cast<double>(i) / n);
+  const std::vector<float2> tw = twiddle_tables(n);
   float2* d = nullptr;
-  TURPY_HIP(hipMalloc(&d, n * sizeof(float2)), "receiver_setup: twiddle table");
-  const hipError_t e = hipMemcpy(d, tw.data(), n * sizeof(float2), hipMemcpyHostToDevice);
+  TURPY_HIP(hipMalloc(&d, tw.size() * sizeof(float2)), "receiver_setup: twiddle table");
+  const hipError_t e = hipMemcpy(d, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     (void)hipFree(d);
     return hip_fail(e, "receiver_setup: twiddle table");

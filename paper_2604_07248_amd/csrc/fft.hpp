@@ -163,7 +163,11 @@ __device__ __forceinline__ void lds_sync() {
   }
 }
 
-// One Stockham pass loading each twiddle right where it is used.
+// One Stockham pass loading each twiddle right where it is used: factor r of
+// sub-position k at tw[(r - 1) NS + k], so that neighbouring lanes (k) read
+// neighbouring words and the factors of a thread sit at constant distances.
+// (Read from one table of the N roots, at r k N / (NS R), the lanes of the
+// second pass fell on one to four banks.)
 template <int N, int E, int R, int NS, bool INV, bool LAST, bool WAVE, class Lds>
 __device__ __forceinline__ void stockham_pass(float2 (&x)[E], const Lds& lds, int t,
                                               const float2* __restrict__ tw) {
@@ -176,11 +180,10 @@ __device__ __forceinline__ void stockham_pass(float2 (&x)[E], const Lds& lds, in
 #pragma unroll
     for (int r = 0; r < R; ++r) v[r] = x[q + B * r];
     if constexpr (NS > 1) {
-      const int k = j & (NS - 1);
-      constexpr int STRIDE = N / (NS * R);
+      const float2* wk = tw + (j & (NS - 1));
 #pragma unroll
       for (int r = 1; r < R; ++r) {
-        const float2 w = tw[r * k * STRIDE];
+        const float2 w = wk[(r - 1) * NS];
         v[r] = INV ? c_mulc(v[r], w) : c_mul(v[r], w);
       }
     }
@@ -213,9 +216,17 @@ __device__ __forceinline__ void stockham_pass(float2 (&x)[E], const Lds& lds, in
 // than one of 16 and the last pass gets a radix of 4 to 16 instead of 2 to 8
 // (column pass, 16 against 8, us: n = 512, R = 256 195 / 190; n = 1024, R = 32
 // 114.5 / 108.2; n = 2048, R = 8 155.7 / 150.9; the synthesis within 1 %).
+constexpr int second_radix_rt(int n, int r2sel) { return r2sel ? r2sel : (n >= 512 ? 8 : n / 16); }
 template <int N, int R2SEL>
-constexpr int second_radix() {
-  return R2SEL ? R2SEL : (N >= 512 ? 8 : N / 16);
+constexpr int second_radix() { return second_radix_rt(N, R2SEL); }
+
+// The twiddle table of a plan: its factors pass by pass, (R2 - 1) x 16 for the
+// second pass and (R3 - 1) x 16 R2 for the third, exp(-2 pi i r k / (NS R));
+// N - 16 entries in all.  A plan's array holds the default radix plan's table
+// and, N entries on, the one of a second pass of radix 4.
+template <int N, int R2SEL>
+__device__ __forceinline__ const float2* plan_twiddles(const float2* tw) {
+  return R2SEL ? tw + N : tw;
 }
 template <int N, int R2SEL>
 constexpr int fft_passes() {
@@ -234,15 +245,16 @@ __device__ __forceinline__ void fft(float2 (&x)[E], const Lds& lds, int t, const
     static_assert(REM1 % R2 == 0 && R2 <= 16 && REM1 / R2 <= 16, "unsupported radix plan");
     constexpr int REM2 = REM1 / R2;
     stockham_pass<N, E, R2, 16, INV, REM2 == 1, WAVE>(x, lds, t, tw);
-    if constexpr (REM2 > 1) stockham_pass<N, E, REM2, 16 * R2, INV, true, WAVE>(x, lds, t, tw);
+    if constexpr (REM2 > 1) stockham_pass<N, E, REM2, 16 * R2, INV, true, WAVE>(x, lds, t, tw + (R2 - 1) * 16);
   }
 }
 
-// Copy the N-entry twiddle table into LDS once per block: the passes then
-// read their per-lane twiddles with LDS loads instead of divergent global
-// gathers.  Block-wide barrier at the end.
-template <int N>
-__device__ __forceinline__ const float2* stage_twiddles(float2* lds_tw, const float2* __restrict__ tw) {
+// Copy the twiddle table into LDS once per block: the passes then read their
+// per-lane twiddles with LDS loads instead of divergent global gathers.
+// Block-wide barrier at the end.
+template <int N, int R2SEL = 0>
+__device__ __forceinline__ const float2* stage_twiddles(float2* lds_tw, const float2* __restrict__ plan_tw) {
+  const float2* tw = plan_twiddles<N, R2SEL>(plan_tw);
   for (int i = threadIdx.x; i < N; i += blockDim.x) lds_tw[i] = tw[i];
   __syncthreads();
   return lds_tw;

@@ -741,7 +741,7 @@ __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
   const float sign = a.conj_table ? -1.0f : 1.0f;
   for (int i = threadIdx.x; i < N; i += blockDim.x) h_lds[i] = make_float2(a.table[i].x, a.table[i].y * sign);
   const float2* chirp = h_lds;
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const float2* tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
   const float2* src = a.in + r * a.in_stride + k1;
   float2 x[kE];
 #pragma unroll
@@ -790,7 +790,7 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a, int slot) {
   const int k1 = strip * K + c;
   const ColLds<K> lds{smem, c};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const float2* tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
   float2 x[kE];
   const uint32_t screen = a.screen + static_cast<uint32_t>(slot);
   const float amp = a.amp[slot];
@@ -913,7 +913,7 @@ __device__ __forceinline__ void synth_solo_body(const SynthArgs& a, int slot) {
     *lo = make_float2((n_lo.x + p_lo.x) * w_lo, (n_lo.y - p_lo.y) * w_lo);
     *hi = make_float2((n_hi.x + p_hi.x) * w_hi, (n_hi.y - p_hi.y) * w_hi);
   };
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const float2* tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
   float2 x[kE];
   if (!edge) {
 #pragma unroll

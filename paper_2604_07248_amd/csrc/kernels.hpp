@@ -17,7 +17,7 @@ constexpr uint32_t TAG_AR_SH = 4;  // AR innovations of the subharmonic coeffici
 enum RowScreen : int { ROW_NO_SCREEN = 0, ROW_SCRATCH = 1, ROW_MATERIALIZED = 2 };
 
 struct RowArgs {
-  const float2* tw;         // twiddles exp(-2 pi i k / N), [N]
+  const float2* tw;         // twiddle tables of the radix plans, [2][N] (twiddle_tables)
   const float2* in;         // field rows, realization r at in + r * in_stride
   int64_t in_stride;        // elements between realizations (0: shared source)
   float2* out;              // [R][N][N]

@@ -15,6 +15,7 @@
 #include <string>
 #include <vector>
 
+#include "fft.hpp"
 #include "kernels.hpp"
 #include "layout.hpp"
 #include "report.hpp"
@@ -58,6 +59,27 @@ inline bool pow2(int n) { return n > 0 && (n & (n - 1)) == 0; }
 inline float2 phasor(double rev) {
   rev -= std::rint(rev);
   return make_float2(static_cast<float>(std::cos(2.0 * kPi * rev)), static_cast<float>(std::sin(2.0 * kPi * rev)));
+}
+
+// The twiddle tables of grid size n, [2][n]: the default radix plan's and that
+// of a second pass of radix 4 (zeros where that plan is not built).  A table
+// holds, for the second pass (NS = 16) and then the third (NS = 16 R2), the
+// factors exp(-2 pi i r k / (NS R)) at (r - 1) NS + k, 0 < r < R, k < NS.
+inline std::vector<float2> twiddle_tables(int n) {
+  std::vector<float2> tw(static_cast<size_t>(2) * n, make_float2(0.0f, 0.0f));
+  for (int variant = 0; variant < 2; ++variant) {
+    const int r2sel = variant ? 4 : 0;
+    if (variant && n != 512 && n != 1024) continue;
+    float2* p = tw.data() + static_cast<size_t>(variant) * n;
+    int ns = 16;
+    for (int pass = 0; pass < 2 && n / ns > 1; ++pass) {
+      const int r = pass == 0 ? second_radix_rt(n, r2sel) : n / ns;
+      for (int f = 1; f < r; ++f)
+        for (int k = 0; k < ns; ++k) *p++ = phasor(-static_cast<double>(f * k) / (static_cast<double>(ns) * r));
+      ns *= r;
+    }
+  }
+  return tw;
 }
 
 inline int signed_bin(int k, int n) { return k < n / 2 ? k : k - n; }
@@ -123,7 +145,7 @@ struct turpy_plan {
   double alpha = 11.0 / 3.0;
   float2 sh_mean_fac[3] = {};
   // device tables (owned)
-  float2* d_tw = nullptr;        // [N]
+  float2* d_tw = nullptr;        // [2][N] (twiddle_tables)
   float2* d_row = nullptr;       // [M+1][N] h_i[k]
   float2* d_col = nullptr;       // [M+1][N] h_i[k] / N
   // angular spectrum: H_as / H_fresnel as a function of q = k0^2 + k1^2 (signed
