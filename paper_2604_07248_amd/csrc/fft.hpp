@@ -233,31 +233,38 @@ constexpr int fft_passes() {
   return N == 16 ? 1 : (N / 16 == second_radix<N, R2SEL>() ? 2 : 3);
 }
 
+// Where a transform reads the factors of its second and third pass.
+struct Twiddles {
+  const float2* second;
+  const float2* third;
+};
+
 template <int N, int E, bool INV, bool WAVE = false, int R2SEL = 0, class Lds>
-__device__ __forceinline__ void fft(float2 (&x)[E], const Lds& lds, int t, const float2* __restrict__ tw) {
+__device__ __forceinline__ void fft(float2 (&x)[E], const Lds& lds, int t, const Twiddles& tw) {
   static_assert(E == 16, "radix plan written for 16 elements per thread");
   static_assert(N >= 16 && N <= 4096 && (N & (N - 1)) == 0, "N must be a power of two in 16..4096");
   static_assert(!WAVE || N / E <= 64, "a wave-local transform needs at most 64 threads");
   constexpr int REM1 = N / 16;
-  stockham_pass<N, E, 16, 1, INV, REM1 == 1, WAVE>(x, lds, t, tw);
+  stockham_pass<N, E, 16, 1, INV, REM1 == 1, WAVE>(x, lds, t, tw.second);
   if constexpr (REM1 > 1) {
     constexpr int R2 = second_radix<N, R2SEL>();
     static_assert(REM1 % R2 == 0 && R2 <= 16 && REM1 / R2 <= 16, "unsupported radix plan");
     constexpr int REM2 = REM1 / R2;
-    stockham_pass<N, E, R2, 16, INV, REM2 == 1, WAVE>(x, lds, t, tw);
-    if constexpr (REM2 > 1) stockham_pass<N, E, REM2, 16 * R2, INV, true, WAVE>(x, lds, t, tw + (R2 - 1) * 16);
+    stockham_pass<N, E, R2, 16, INV, REM2 == 1, WAVE>(x, lds, t, tw.second);
+    if constexpr (REM2 > 1) stockham_pass<N, E, REM2, 16 * R2, INV, true, WAVE>(x, lds, t, tw.third);
   }
 }
 
-// Copy the twiddle table into LDS once per block: the passes then read their
-// per-lane twiddles with LDS loads instead of divergent global gathers.
-// Block-wide barrier at the end.
-template <int N, int R2SEL = 0>
-__device__ __forceinline__ const float2* stage_twiddles(float2* lds_tw, const float2* __restrict__ plan_tw) {
+// Copy the twiddle table into LDS once per block (without THIRD, the second
+// pass's part of it: the third pass then reads global memory).  Block-wide
+// barrier at the end.
+template <int N, int R2SEL = 0, bool THIRD = true>
+__device__ __forceinline__ Twiddles stage_twiddles(float2* lds_tw, const float2* __restrict__ plan_tw) {
   const float2* tw = plan_twiddles<N, R2SEL>(plan_tw);
-  for (int i = threadIdx.x; i < N; i += blockDim.x) lds_tw[i] = tw[i];
+  constexpr int second = (second_radix<N, R2SEL>() - 1) * 16;
+  for (int i = threadIdx.x; i < (THIRD ? N : second); i += blockDim.x) lds_tw[i] = tw[i];
   __syncthreads();
-  return lds_tw;
+  return Twiddles{lds_tw, (THIRD ? lds_tw : tw) + second};
 }
 
 // Barriers executed by fft<N, 16, ...>: a group with no transform to do calls

@@ -125,7 +125,7 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
   const int64_t j = blockIdx.y;
   const RowLds lds{smem + g * RowLds::words(N)};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const size_t row_off = static_cast<size_t>(i0) * N;
 
@@ -252,7 +252,7 @@ __global__ __launch_bounds__(row_block<N>()) void row_pass_kernel(RowArgs a) { r
 template <int N, bool BWD>
 __device__ __forceinline__ void finish_row(const RowArgs& a, float2 (&x)[kE], const float (&ph)[kE],
                                            const float2 (&wck)[kE], bool want_ck, bool writes, size_t ck, size_t cw,
-                                           float2* dst, const RowLds& lds, int t, const float2* tw) {
+                                           float2* dst, const RowLds& lds, int t, const Twiddles& tw) {
   constexpr int T = N / kE;
   constexpr bool WV = T <= 64;
   if constexpr (!BWD) {
@@ -328,8 +328,17 @@ __device__ __forceinline__ void row_pair_body(const RowArgs& a) {
   const bool writes = role == 0 || has_b;
   const RowLds lds{smem + (role * G + g) * RowLds::words(N)};
   float* handoff = reinterpret_cast<float*>(smem + (G + g) * RowLds::words(N));  // half B's buffer
-  __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  // At N = 2048 the third pass's factors (15 KB, read once per transform, unit
+  // stride over the lanes) come from the vector cache: a block there is one row
+  // of each realization, and staging the table cost it as much traffic as the
+  // rows themselves and a third of its LDS (three fields through 12 screens
+  // 2.25 -> 2.13 ms; a serving mix 26.3 -> 25.0 ms).  On smaller grids, in the
+  // other row schedules and in the column passes the cache is the busier unit:
+  // the same choice for N = 512 and 1024 made the forward pass 5 % slower, in
+  // the column passes too 10 %.
+  constexpr bool kStageThird = N <= 1024;
+  __shared__ float2 tw_lds[kStageThird ? N : (second_radix<N, 0>() - 1) * 16];
+  const Twiddles tw = stage_twiddles<N, 0, kStageThird>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const size_t rplane = a.solo ? plane / 2 : plane;  // from one realization's rows to the next's
   const int64_t in_stride = a.solo ? static_cast<int64_t>(rplane) : a.in_stride;
@@ -500,7 +509,7 @@ __device__ __forceinline__ void row_relay_body(const RowArgs& a) {
   const int row1 = row0 + G;                // and in group 1
   const RowLds lds{smem + (w * G + g) * RowLds::words(N)};
   float* hand = handoff_rows + g * N + t;
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const size_t rplane = a.solo ? plane / 2 : plane;  // from one realization's rows to the next's
   const int64_t in_stride = a.solo ? static_cast<int64_t>(rplane) : a.in_stride;
@@ -655,7 +664,7 @@ __device__ __forceinline__ void row_trio_body(const RowArgs& a) {
       for (int m = 0; m < kE; ++m) wck[m] = ld_s<true>(a.ckpt_in + cw_row + t + T * m);
     }
   }
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   if (role == 0) {
     fft<N, kE, true, true>(x, lds, t, tw);
     add_subharmonics<N>(a, j, i0, t, x);
@@ -741,7 +750,7 @@ __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
   const float sign = a.conj_table ? -1.0f : 1.0f;
   for (int i = threadIdx.x; i < N; i += blockDim.x) h_lds[i] = make_float2(a.table[i].x, a.table[i].y * sign);
   const float2* chirp = h_lds;
-  const float2* tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
   const float2* src = a.in + r * a.in_stride + k1;
   float2 x[kE];
 #pragma unroll
@@ -790,7 +799,7 @@ __device__ __forceinline__ void synth_col_body(const SynthArgs& a, int slot) {
   const int k1 = strip * K + c;
   const ColLds<K> lds{smem, c};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
   float2 x[kE];
   const uint32_t screen = a.screen + static_cast<uint32_t>(slot);
   const float amp = a.amp[slot];
@@ -913,7 +922,7 @@ __device__ __forceinline__ void synth_solo_body(const SynthArgs& a, int slot) {
     *lo = make_float2((n_lo.x + p_lo.x) * w_lo, (n_lo.y - p_lo.y) * w_lo);
     *hi = make_float2((n_hi.x + p_hi.x) * w_hi, (n_hi.y - p_hi.y) * w_hi);
   };
-  const float2* tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
   float2 x[kE];
   if (!edge) {
 #pragma unroll
@@ -1123,7 +1132,7 @@ __global__ __launch_bounds__(moment_chunks(N) * (N / kE)) void row_moments_kerne
   const int c = threadIdx.x / T;
   const int t = threadIdx.x % T;
   const RowLds lds{smem + c * RowLds::words(N)};
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const size_t row_off = static_cast<size_t>(blockIdx.x) * N;
   const int64_t lo = c * a.R / C, hi = (c + 1) * a.R / C;

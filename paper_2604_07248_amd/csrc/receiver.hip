@@ -42,7 +42,7 @@ __global__ __launch_bounds__(row_block<N>()) void recv_row_in_kernel(RecvArgs a)
   const int64_t b = blockIdx.y;
   const RowLds lds{smem + g * RowLds::words(N)};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t row = static_cast<size_t>(i0) * N;
   const float2* src = a.u + b * static_cast<int64_t>(N) * N + row;
   float2 x[kE];
@@ -72,7 +72,7 @@ __global__ __launch_bounds__(col_block<N>()) void recv_col_kernel(RecvArgs a) {
   const int k1 = strip * K + c;
   const ColLds<K> lds{smem, c};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const float2* src = a.in + b * plane + k1;
   float2 x[kE];
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(col_block<N>()) void recv_col_grad_kernel(RecvArgs 
   const int k1 = strip * K + c;
   const ColLds<K> lds{smem, c};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const int64_t per = (a.batch + a.chunks - 1) / a.chunks;
   const int64_t b0 = chunk * per, b1 = b0 + per < a.batch ? b0 + per : a.batch;
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(row_block<N>()) void recv_row_grad_kernel(RecvArgs 
   const int chunk = blockIdx.y;
   const RowLds lds{smem + g * RowLds::words(N)};
   __shared__ float2 tw_lds[N];
-  const float2* tw = stage_twiddles<N>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N>(tw_lds, a.tw);
   const size_t plane = static_cast<size_t>(N) * N;
   const size_t row = static_cast<size_t>(i0) * N;
   const int64_t per = (a.batch + a.chunks - 1) / a.chunks;
