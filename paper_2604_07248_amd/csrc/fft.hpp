@@ -119,18 +119,22 @@ struct RowLds {
 };
 
 // LDS addressing of a strip of K columns transformed along the row index:
-// element (row, c) at row*K + c.
-template <int K>
+// element (row, c) at row*K + c.  With SWZ the rows trade places inside groups
+// of 32/K (256 bytes, one word per bank) by the bits that the lanes of the
+// first pass's scatter differ in, which would otherwise all fall on K banks.
+template <int K, bool SWZ = false>
 struct ColLds {
   float2* base;
   int c;
-  __device__ __forceinline__ float2& operator[](int i) const { return base[i * K + c]; }
+  static constexpr int kMask = SWZ ? 32 / K - 1 : 0;
+  static __device__ __forceinline__ int row(int i) { return i ^ ((i >> 4) & kMask); }
+  __device__ __forceinline__ float2& operator[](int i) const { return base[row(i) * K + c]; }
   static constexpr int words(int n) { return n * K; }
   template <int T>
-  static constexpr bool strided_ok() { return true; }
+  static constexpr bool strided_ok() { return T % (16 * (kMask + 1)) == 0 || !SWZ; }
   template <int T>
   static constexpr int step() { return T * K; }
-  __device__ __forceinline__ float2* strided(int t) const { return base + t * K + c; }
+  __device__ __forceinline__ float2* strided(int t) const { return base + row(t) * K + c; }
 };
 
 // Read the strided layout x[m] = element t + T m back from LDS.

@@ -734,6 +734,10 @@ template <int N, int ANGULAR, int K, int R2SEL>
 __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
   constexpr int T = N / kE;
   constexpr int STRIPS = N / K;
+  // lean: the chirp and the third pass's twiddles come from the vector cache
+  // instead of LDS tables, so that two blocks share a CU, and the strip's rows
+  // are swizzled (4 columns would put the first pass's scatter on 8 banks)
+  constexpr bool kLean = col_lean(N, K);
   __shared__ float2 smem[ColLds<K>::words(N)];
   TURPY_LDS_INIT(smem);
   int strip;
@@ -742,15 +746,16 @@ __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
   const int c = threadIdx.x % K;
   const int t = threadIdx.x / K;
   const int k1 = strip * K + c;
-  const ColLds<K> lds{smem, c};
-  __shared__ float2 tw_lds[N];
-  __shared__ float2 h_lds[N];
+  const ColLds<K, kLean> lds{smem, c};
+  __shared__ float2 tw_lds[kLean ? (second_radix<N, R2SEL>() - 1) * 16 : N];
+  __shared__ float2 h_lds[kLean ? 1 : N];
   TURPY_LDS_INIT(h_lds);
   // h, conjugated where the adjoint asks for it (the correction below is too)
   const float sign = a.conj_table ? -1.0f : 1.0f;
-  for (int i = threadIdx.x; i < N; i += blockDim.x) h_lds[i] = make_float2(a.table[i].x, a.table[i].y * sign);
+  if constexpr (!kLean)
+    for (int i = threadIdx.x; i < N; i += blockDim.x) h_lds[i] = make_float2(a.table[i].x, a.table[i].y * sign);
   const float2* chirp = h_lds;
-  const Twiddles tw = stage_twiddles<N, R2SEL>(tw_lds, a.tw);
+  const Twiddles tw = stage_twiddles<N, R2SEL, !kLean>(tw_lds, a.tw);
   const float2* src = a.in + r * a.in_stride + k1;
   float2 x[kE];
 #pragma unroll
@@ -759,7 +764,9 @@ __device__ __forceinline__ void col_pass_body(const ColArgs& a) {
 #pragma unroll
   for (int m = 0; m < kE; ++m) {
     const int k0 = t + T * m;
-    float2 h = chirp[k0];
+    float2 h;
+    if constexpr (kLean) h = make_float2(a.table[k0].x, a.table[k0].y * sign);
+    else h = chirp[k0];
     if constexpr (ANGULAR != TF_FRESNEL_ONLY) {
       const float2 f = angular_correction<ANGULAR>(a, k0, k1, N);
       h = c_mul(h, make_float2(f.x, f.y * sign));

@@ -37,7 +37,15 @@ constexpr int fill_width(int n, int64_t planes, int widest) {
 constexpr int widest_col(int n) { return n >= 1024 ? 8 : (n >= 128 ? 16 : 8); }
 constexpr int widest_synth(int n) { return n >= 1024 ? 4 : (n >= 512 ? 8 : widest_col(n)); }
 constexpr int widest_ar(int n) { return n >= 2048 ? 8 : (n >= 128 ? 16 : 8); }
-constexpr int default_col_width(int n, int64_t planes) { return fill_width(n, planes, widest_col(n)); }
+// At N = 2048 one block of 8 columns takes a CU's whole LDS, and its waves wait
+// at the same barriers; two lean blocks of 4 columns (col_lean) overlap.  They
+// pay from three planes on (us for 8 / 4 columns: one plane 22.9 / 25.6, two
+// 40.3 / 39.8, three 57.0 / 54.6, eight 145.5 / 140.2; a serving mix, one plane
+// a launch on four streams, 24.7 / 25.5 ms).
+constexpr bool col_lean(int n, int k) { return n == 2048 && k == 4; }
+constexpr int default_col_width(int n, int64_t planes) {
+  return n == 2048 && planes >= 3 ? 4 : fill_width(n, planes, widest_col(n));
+}
 constexpr int default_synth_width(int n, int64_t planes) { return fill_width(n, planes, widest_synth(n)); }
 constexpr int default_ar_width(int n, int64_t planes) { return fill_width(n, planes, widest_ar(n)); }
 // Grouped launches and the receiver, whose members together fill the chip.
