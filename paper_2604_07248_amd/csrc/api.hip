@@ -455,9 +455,11 @@ turpy_status turpy_screen_generate(turpy_plan* pl, uint64_t seed, int64_t t, flo
   const Ws w = carve(pl, ws, TURPY_SCREENS_SPECTRA);
   if (pl->sh_levels > 0) TURPY_HIP(enqueue_sh(pl, seed, static_cast<uint32_t>(t), w, st), "screen_generate: sh");
   int ready = -1;
-  for (int s = 0; s < pl->M; ++s) {
+  for (int s = 0; s < pl->M; s += w.batch) {  // the screens of one synthesis launch, finished by one row launch
     TURPY_HIP(enqueue_screen_col(pl, seed, static_cast<uint32_t>(t), s, nullptr, w, &ready, st), "screen_generate: col");
     RowArgs a = base_row(pl);
+    a.screen_count = std::min(w.batch, pl->M - s);
+    a.screen_stride = w.screen_stride;
     screen_fields(pl, TURPY_SCREENS_SYNTH, nullptr, w, s, &a);
     a.screen_mode = ROW_SCRATCH;
     a.in = nullptr;  // no field: the row kernel only emits the phases

@@ -244,7 +244,13 @@ __device__ __forceinline__ void row_pass_body(const RowArgs& a) {
 }
 
 template <int N, int SCREEN, bool BWD>
-__global__ __launch_bounds__(row_block<N>()) void row_pass_kernel(RowArgs a) { row_pass_body<N, SCREEN, BWD>(a); }
+__global__ __launch_bounds__(row_block<N>()) void row_pass_kernel(RowArgs a) {
+  if constexpr (SCREEN == ROW_SCRATCH && !BWD) {  // the screens of a phase_out launch
+    a.screen += static_cast<int>(blockIdx.z);
+    a.scratch += blockIdx.z * a.screen_stride;
+  }
+  row_pass_body<N, SCREEN, BWD>(a);
+}
 
 // The end of a screen row: the pointwise step of Eq. 1 (or its adjoint) at the
 // phases ph, the checkpoint, the forward transform and the store (none of the
@@ -1744,8 +1750,10 @@ hipError_t row_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
   } else if (a.phase_out || (pair_rows<N>() * (N / kE)) % 64 != 0 || solo_forward<N>(a)) {
     // screen output, grids too small for the two halves to sit in separate
     // waves, or a single realization on the pair schedule
-    if (a.screen_mode == ROW_SCRATCH && !a.backward)
+    if (a.screen_mode == ROW_SCRATCH && !a.backward) {
+      if (a.phase_out && a.screen_count > 1) grid.z = static_cast<uint32_t>(a.screen_count);
       hipLaunchKernelGGL((row_pass_kernel<N, ROW_SCRATCH, false>), grid, block, 0, s, a);
+    }
     else if (a.screen_mode == ROW_SCRATCH)
       hipLaunchKernelGGL((row_pass_kernel<N, ROW_SCRATCH, true>), grid, block, 0, s, a);
     else if (!a.backward)

@@ -43,6 +43,10 @@ struct RowArgs {
   int ckpt_single;          // 1: ckpt_out / ckpt_in hold this screen only, [R][N][N]
   float* grad_screens;      // backward: [R][M][N][N] dL/dphi, or NULL
   float* phase_out;         // [R][M][N][N] radians: write the screens themselves, or NULL
+  // with phase_out: consecutive screens of the launch (0 or 1: `screen` alone)
+  // and the elements from one screen's scratch planes to the next's
+  int screen_count;
+  size_t screen_stride;
   int waves;                // occupancy hint of the screen row passes (2, 3, 4; 0: the default)
   // One realization with solo scratch (SynthArgs::solo): its rows y and
   // y + N/2 take the places of a pair's two realizations, N/2 rows apiece

@@ -38,7 +38,7 @@ def test_batches_match_oracle(gpu_lib, n, r, m, sh):
     ref, ref_ck = opr.propagate(u0.astype(np.complex128), path, phi)
     ref_in, ref_phi = opr.propagate_adjoint(g.astype(np.complex128), path, phi, ref_ck)
     errs = [rel_l2(a.cpu().numpy(), b) for a, b in ((out, ref), (plain, ref), (ck, ref_ck), (g_in, ref_in),
-                                                    (g_phi, ref_phi))]
+                                                    (g_phi, ref_phi), (plan.screens(5, t=2), phi))]
     say(f"[synth batch] n={n} R={r} M={m}: " + " ".join(f"{e:.1e}" for e in errs))
     assert max(errs) < TOL
     plan.close()
