@@ -60,81 +60,53 @@ __device__ __forceinline__ void load_field_row(float2 (&v)[kE], const float2* p,
   }
 }
 
-// cos and sin of 2 pi m / (16 3^(p + 1)): how far element m of a thread (N/16
-// columns on) turns level p's phasor from element 0's.
-constexpr float kShCos[3][kE] = {
-    {1.000000000f, 0.991444861f, 0.965925826f, 0.923879533f, 0.866025404f, 0.793353340f, 0.707106781f, 0.608761429f,
-     0.500000000f, 0.382683432f, 0.258819045f, 0.130526192f, 0.000000000f, -0.130526192f, -0.258819045f, -0.382683432f},
-    {1.000000000f, 0.999048222f, 0.996194698f, 0.991444861f, 0.984807753f, 0.976296007f, 0.965925826f, 0.953716951f,
-     0.939692621f, 0.923879533f, 0.906307787f, 0.887010833f, 0.866025404f, 0.843391446f, 0.819152044f, 0.793353340f},
-    {1.000000000f, 0.999894232f, 0.999576950f, 0.999048222f, 0.998308158f, 0.997356917f, 0.996194698f, 0.994821748f,
-     0.993238358f, 0.991444861f, 0.989441639f, 0.987229113f, 0.984807753f, 0.982178070f, 0.979340622f, 0.976296007f}};
-constexpr float kShSin[3][kE] = {
-    {0.000000000f, 0.130526192f, 0.258819045f, 0.382683432f, 0.500000000f, 0.608761429f, 0.707106781f, 0.793353340f,
-     0.866025404f, 0.923879533f, 0.965925826f, 0.991444861f, 1.000000000f, 0.991444861f, 0.965925826f, 0.923879533f},
-    {0.000000000f, 0.043619387f, 0.087155743f, 0.130526192f, 0.173648178f, 0.216439614f, 0.258819045f, 0.300705800f,
-     0.342020143f, 0.382683432f, 0.422618262f, 0.461748613f, 0.500000000f, 0.537299608f, 0.573576436f, 0.608761429f},
-    {0.000000000f, 0.014543898f, 0.029084719f, 0.043619387f, 0.058144829f, 0.072657971f, 0.087155743f, 0.101635078f,
-     0.116092914f, 0.130526192f, 0.144931859f, 0.159306868f, 0.173648178f, 0.187952754f, 0.202217572f, 0.216439614f}};
-
-// Level P of the subharmonics along screen row i0: the field there is
-// d0 + sa cos + i sb sin of the column's phase; d0 goes to `flat`.  Element 0's
-// phasor is the only one loaded: along a thread's elements the phase advances by
-// constants, so a level costs four multiply-adds per element and no memory
-// (loading every phasor added 48 loads to the 80 of a row pair; 256 realizations
-// at N = 512 with three levels 6.02 -> 5.72 ms for 10 screens).
-template <int N, int P>
-__device__ __forceinline__ void add_level(const RowArgs& a, const float2* cp, int i0, int t, float2 (&z)[kE],
-                                          float2* flat) {
-  const float2* ph = a.sh_phasor + static_cast<size_t>(P) * N;
-  float2 d0, sa, sb;
-  auto along = [&](int row) {
-    const float2 ey = ph[row];
-    const float2 eyc = make_float2(ey.x, -ey.y);
-    // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
-    const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
-    d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
-    const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
-    sa = c_add(dp, dm);
-    sb = c_sub(dp, dm);
-  };
-  const float2 ex = ph[t];
-  // Re((sa.re + i sb.im) ex) and Re((sa.im - i sb.re) ex), the latter for a solo
-  // screen the former of row i0 + N/2
-  float2 fy;
-  if (a.solo) {
-    along(i0 + N / 2);
-    fy = c_mul(make_float2(sa.x, sb.y), ex);
-    flat->y += d0.x;
-    along(i0);
-  } else {
-    along(i0);
-    fy = c_mul(make_float2(sa.y, -sb.x), ex);
-    flat->y += d0.y;
-  }
-  flat->x += d0.x;
-  const float2 fx = c_mul(make_float2(sa.x, sb.y), ex);
-#pragma unroll
-  for (int m = 0; m < kE; ++m) {
-    z[m].x = __builtin_fmaf(fx.x, kShCos[P][m], __builtin_fmaf(-fx.y, kShSin[P][m], z[m].x));
-    z[m].y = __builtin_fmaf(fy.x, kShCos[P][m], __builtin_fmaf(-fy.y, kShSin[P][m], z[m].y));
-  }
-}
-
 // Subharmonics and piston (Eq. 2-3) added to screen row i0 of pair j after its
 // inverse transform.  Solo: z holds the real screen's rows i0 (re) and
 // i0 + N/2 (im), and both take the real part of the subharmonic field.
 template <int N>
 __device__ __forceinline__ void add_subharmonics(const RowArgs& a, int64_t j, int i0, int t, float2 (&z)[kE]) {
+  constexpr int T = N / kE;
   if (a.sh_levels <= 0) return;
   const float2* c = a.sh + (static_cast<size_t>(j) * a.M + a.screen) * 32;
-  float2 flat = c_scale(c[24], -a.sh_scale);  // minus the mean, plus the levels' parts that do not vary along the row
-  if (a.solo) flat.y = flat.x;
-  add_level<N, 0>(a, c, i0, t, z, &flat);
-  if (a.sh_levels > 1) add_level<N, 1>(a, c + 8, i0, t, z, &flat);
-  if (a.sh_levels > 2) add_level<N, 2>(a, c + 16, i0, t, z, &flat);
+  float2 mean = c_scale(c[24], a.sh_scale);
+  if (a.solo) mean.y = mean.x;
 #pragma unroll
-  for (int m = 0; m < kE; ++m) z[m] = c_add(z[m], flat);
+  for (int m = 0; m < kE; ++m) z[m] = c_sub(z[m], mean);
+  for (int p = 0; p < a.sh_levels; ++p) {
+    const float2* cp = c + 8 * p;
+    const float2* ph = a.sh_phasor + static_cast<size_t>(p) * N;
+    // the level's field along row `row`: d0 + sa ex.re + i sb ex.im
+    float2 d0, sa, sb;
+    auto along = [&](int row) {
+      const float2 ey = ph[row];
+      const float2 eyc = make_float2(ey.x, -ey.y);
+      // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
+      const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
+      d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
+      const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
+      sa = c_add(dp, dm);
+      sb = c_sub(dp, dm);
+    };
+    float2 e0, ea, eb;
+    if (a.solo) {
+      along(i0 + N / 2);
+      e0 = make_float2(0.0f, d0.x);
+      ea = make_float2(0.0f, sa.x);
+      eb = make_float2(-sb.y, 0.0f);
+      along(i0);
+    } else {
+      along(i0);
+      e0 = d0;
+      ea = sa;
+      eb = sb;
+    }
+#pragma unroll
+    for (int m = 0; m < kE; ++m) {
+      const float2 ex = (ph + t)[T * m];
+      z[m].x += d0.x + sa.x * ex.x - sb.y * ex.y;
+      z[m].y += e0.y + ea.y * ex.x + eb.x * ex.y;
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
