@@ -165,7 +165,7 @@ turpy_status turpy_plan_create(turpy_plan** out, const turpy_path* p, uint32_t f
     double mr = 0, mi = 0;
     for (int i = 0; i < n; ++i) {
       const double rev = (i - n / 2) * scale;
-      shp[static_cast<size_t>(lv) * n + i] = phasor(rev);
+      shp[static_cast<size_t>(lv) * n + sh_slot(n, i)] = phasor(rev);
       mr += std::cos(2.0 * kPi * rev);
       mi += std::sin(2.0 * kPi * rev);
     }

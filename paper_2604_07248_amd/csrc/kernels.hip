@@ -78,7 +78,7 @@ __device__ __forceinline__ void add_subharmonics(const RowArgs& a, int64_t j, in
     // the level's field along row `row`: d0 + sa ex.re + i sb ex.im
     float2 d0, sa, sb;
     auto along = [&](int row) {
-      const float2 ey = ph[row];
+      const float2 ey = ph[sh_slot(N, row)];
       const float2 eyc = make_float2(ey.x, -ey.y);
       // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
       const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
@@ -101,10 +101,12 @@ __device__ __forceinline__ void add_subharmonics(const RowArgs& a, int64_t j, in
       eb = sb;
     }
 #pragma unroll
-    for (int m = 0; m < kE; ++m) {
-      const float2 ex = (ph + t)[T * m];
-      z[m].x += d0.x + sa.x * ex.x - sb.y * ex.y;
-      z[m].y += e0.y + ea.y * ex.x + eb.x * ex.y;
+    for (int m = 0; m < kE; m += 2) {
+      const float4 e2 = (reinterpret_cast<const float4*>(ph) + t)[T * (m / 2)];
+      z[m].x += d0.x + sa.x * e2.x - sb.y * e2.y;
+      z[m].y += e0.y + ea.y * e2.x + eb.x * e2.y;
+      z[m + 1].x += d0.x + sa.x * e2.z - sb.y * e2.w;
+      z[m + 1].y += e0.y + ea.y * e2.z + eb.x * e2.w;
     }
   }
 }

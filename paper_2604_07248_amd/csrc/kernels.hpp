@@ -36,7 +36,7 @@ struct RowArgs {
   int sh_levels;            // 0..3
   const float2* sh;         // [P][M][32] subharmonic coefficients, [24] = their grid mean
   float sh_scale;           // to revolutions: 1 (synthesised) or 1/(2 pi) (AR state, radians)
-  const float2* sh_phasor;  // [3][N] exp(2 pi i (i - N/2) / (N 3^p))
+  const float2* sh_phasor;  // [3][N] exp(2 pi i (i - N/2) / (N 3^p)) at sh_slot(N, i)
   int backward;             // 0: W = U e^{i phi}; 1: adjoint (read checkpoint, write dL/dphi, e^{-i phi})
   float2* ckpt_out;         // [R][M][N][N] field after the screen, or NULL (backward: as rebuilt)
   const float2* ckpt_in;    // backward: same layout

@@ -41,7 +41,7 @@ constexpr int widest_ar(int n) { return n >= 2048 ? 8 : (n >= 128 ? 16 : 8); }
 // at the same barriers; two lean blocks of 4 columns (col_lean) overlap.  They
 // pay from three planes on (us for 8 / 4 columns: one plane 22.9 / 25.6, two
 // 40.3 / 39.8, three 57.0 / 54.6, eight 145.5 / 140.2; a serving mix, one plane
-// a launch on four streams, 24.7 / 25.5 ms).
+// a launch beside other streams', 24.7 / 25.5 ms).
 constexpr bool col_lean(int n, int k) { return n == 2048 && k == 4; }
 constexpr int default_col_width(int n, int64_t planes) {
   return n == 2048 && planes >= 3 ? 4 : fill_width(n, planes, widest_col(n));
@@ -104,6 +104,16 @@ template <int N>
 constexpr int relay_block() { return 2 * relay_rows<N>() * (N / kE); }
 template <int N>
 constexpr bool relay_fits() { return (relay_rows<N>() * (N / kE)) % 64 == 0; }
+
+// Place of subharmonic phasor i in its level's table: the phasors of a row
+// pass's thread, n / 16 apart, lie in pairs, so that one load brings two.  The
+// row passes wait on their loads' issue: 24 loads for three levels instead of
+// 48 beside the 80 of a row pair took 256 realizations at N = 512 with 10
+// screens from 6.18 to 6.13 ms, 3 at N = 2048 with 12 from 2.09 to 2.06 ms.
+__host__ __device__ constexpr int sh_slot(int n, int i) {
+  const int t = n / kE;
+  return ((i / t / 2) * t + i % t) * 2 + i / t % 2;
+}
 
 // Grids on which a single realization's real screen is synthesised on its own
 // (SynthArgs::solo): the row passes' halves must be whole waves on N/2 rows.
