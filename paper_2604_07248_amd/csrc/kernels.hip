@@ -72,7 +72,12 @@ __device__ __forceinline__ void add_subharmonics(const RowArgs& a, int64_t j, in
   if (a.solo) mean.y = mean.x;
 #pragma unroll
   for (int m = 0; m < kE; ++m) z[m] = c_sub(z[m], mean);
-  for (int p = 0; p < a.sh_levels; ++p) {
+  // unrolled, so that a level's loads are under way while the one before it is
+  // added (one 256 x 256 realization 157 -> 153 us, 256 realizations at N = 512
+  // 6.02 -> 5.97 ms, ten screens each)
+#pragma unroll
+  for (int p = 0; p < 3; ++p) {
+    if (p >= a.sh_levels) break;
     const float2* cp = c + 8 * p;
     const float2* ph = a.sh_phasor + static_cast<size_t>(p) * N;
     // the level's field along row `row`: d0 + sa ex.re + i sb ex.im
