@@ -60,60 +60,97 @@ __device__ __forceinline__ void load_field_row(float2 (&v)[kE], const float2* p,
   }
 }
 
+// One subharmonic level along screen row i0: the pair's screens there are
+// f[0] + f[1] ex.re - f[2] ex.im and f[3] + f[4] ex.re + f[5] ex.im at a column
+// of phasor ex.  Solo: row i0 of the real screen and its row i0 + N/2.
+template <int N>
+__device__ __forceinline__ void level_along(const RowArgs& a, const float2* cp, const float2* ph, int i0,
+                                            float (&f)[6]) {
+  float2 d0, sa, sb;
+  auto along = [&](int row) {
+    const float2 ey = ph[sh_slot(N, row)];
+    const float2 eyc = make_float2(ey.x, -ey.y);
+    // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
+    const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
+    d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
+    const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
+    sa = c_add(dp, dm);
+    sb = c_sub(dp, dm);
+  };
+  if (a.solo) {
+    along(i0 + N / 2);
+    f[3] = d0.x;
+    f[4] = sa.x;
+    f[5] = -sb.y;
+    along(i0);
+  } else {
+    along(i0);
+    f[3] = d0.y;
+    f[4] = sa.y;
+    f[5] = sb.x;
+  }
+  f[0] = d0.x;
+  f[1] = sa.x;
+  f[2] = sb.y;
+}
+
+// The value of lane P of the lane's four.
+template <int P>
+__device__ __forceinline__ float quad_lane(float v) {
+  return __builtin_bit_cast(
+      float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), P * 0x55, 0xF, 0xF, true));
+}
+
 // Subharmonics and piston (Eq. 2-3) added to screen row i0 of pair j after its
 // inverse transform.  Solo: z holds the real screen's rows i0 (re) and
 // i0 + N/2 (im), and both take the real part of the subharmonic field.
 template <int N>
 __device__ __forceinline__ void add_subharmonics(const RowArgs& a, int64_t j, int i0, int t, float2 (&z)[kE]) {
   constexpr int T = N / kE;
+  // From N = 64 four lanes share a row: each works out one level's part along the
+  // row and hands it to the other three, instead of all of them all levels (256
+  // realizations, N = 512, ten screens of three levels 5.93 -> 5.81 ms; one
+  // 256 x 256 realization 154 -> 150 us).
+  constexpr bool QUADS = T % 4 == 0;
   if (a.sh_levels <= 0) return;
   const float2* c = a.sh + (static_cast<size_t>(j) * a.M + a.screen) * 32;
   float2 mean = c_scale(c[24], a.sh_scale);
   if (a.solo) mean.y = mean.x;
+  float own[6];
+  if constexpr (QUADS) {
+    const int lv = min(t % 4, a.sh_levels - 1);
+    level_along<N>(a, c + 8 * lv, a.sh_phasor + static_cast<size_t>(lv) * N, i0, own);
+  }
 #pragma unroll
   for (int m = 0; m < kE; ++m) z[m] = c_sub(z[m], mean);
+  auto add = [&](int p, const float (&f)[6]) {
+    const float4* ph = reinterpret_cast<const float4*>(a.sh_phasor + static_cast<size_t>(p) * N) + t;
+#pragma unroll
+    for (int m = 0; m < kE; m += 2) {
+      const float4 e2 = ph[T * (m / 2)];
+      z[m].x += f[0] + f[1] * e2.x - f[2] * e2.y;
+      z[m].y += f[3] + f[4] * e2.x + f[5] * e2.y;
+      z[m + 1].x += f[0] + f[1] * e2.z - f[2] * e2.w;
+      z[m + 1].y += f[3] + f[4] * e2.z + f[5] * e2.w;
+    }
+  };
   // unrolled, so that a level's loads are under way while the one before it is
   // added (one 256 x 256 realization 157 -> 153 us, 256 realizations at N = 512
   // 6.02 -> 5.97 ms, ten screens each)
+  float f[6];
+  auto level = [&](auto P) {
+    constexpr int p = decltype(P)::value;
+    if constexpr (QUADS) {
 #pragma unroll
-  for (int p = 0; p < 3; ++p) {
-    if (p >= a.sh_levels) break;
-    const float2* cp = c + 8 * p;
-    const float2* ph = a.sh_phasor + static_cast<size_t>(p) * N;
-    // the level's field along row `row`: d0 + sa ex.re + i sb ex.im
-    float2 d0, sa, sb;
-    auto along = [&](int row) {
-      const float2 ey = ph[sh_slot(N, row)];
-      const float2 eyc = make_float2(ey.x, -ey.y);
-      // offsets (m, n): 0 (-1,-1) 1 (-1,0) 2 (-1,1) 3 (0,-1) 4 (0,1) 5 (1,-1) 6 (1,0) 7 (1,1)
-      const float2 dm = c_scale(c_add(c_add(c_mul(cp[0], eyc), cp[3]), c_mul(cp[5], ey)), a.sh_scale);
-      d0 = c_scale(c_add(c_mul(cp[1], eyc), c_mul(cp[6], ey)), a.sh_scale);
-      const float2 dp = c_scale(c_add(c_add(c_mul(cp[2], eyc), cp[4]), c_mul(cp[7], ey)), a.sh_scale);
-      sa = c_add(dp, dm);
-      sb = c_sub(dp, dm);
-    };
-    float2 e0, ea, eb;
-    if (a.solo) {
-      along(i0 + N / 2);
-      e0 = make_float2(0.0f, d0.x);
-      ea = make_float2(0.0f, sa.x);
-      eb = make_float2(-sb.y, 0.0f);
-      along(i0);
+      for (int i = 0; i < 6; ++i) f[i] = quad_lane<p>(own[i]);
     } else {
-      along(i0);
-      e0 = d0;
-      ea = sa;
-      eb = sb;
+      level_along<N>(a, c + 8 * p, a.sh_phasor + static_cast<size_t>(p) * N, i0, f);
     }
-#pragma unroll
-    for (int m = 0; m < kE; m += 2) {
-      const float4 e2 = (reinterpret_cast<const float4*>(ph) + t)[T * (m / 2)];
-      z[m].x += d0.x + sa.x * e2.x - sb.y * e2.y;
-      z[m].y += e0.y + ea.y * e2.x + eb.x * e2.y;
-      z[m + 1].x += d0.x + sa.x * e2.z - sb.y * e2.w;
-      z[m + 1].y += e0.y + ea.y * e2.z + eb.x * e2.w;
-    }
-  }
+    add(p, f);
+  };
+  level(std::integral_constant<int, 0>());
+  if (a.sh_levels > 1) level(std::integral_constant<int, 1>());
+  if (a.sh_levels > 2) level(std::integral_constant<int, 2>());
 }
 
 // ---------------------------------------------------------------------------
