@@ -66,7 +66,8 @@ inline float2 phasor(double rev) {
 // holds, for the second pass (NS = 16) and then the third (NS = 16 R2), the
 // factors exp(-2 pi i r k / (NS R)) at (r - 1) NS + k, 0 < r < R, k < NS.
 inline std::vector<float2> twiddle_tables(int n) {
-  std::vector<float2> tw(static_cast<size_t>(2) * n, make_float2(0.0f, 0.0f));
+  std::vector<float2> tw(static_cast<size_t>(2) * n, make_float2(0.0f, 0.0f)), root(n);
+  for (int i = 0; i < n; ++i) root[i] = phasor(-static_cast<double>(i) / n);
   for (int variant = 0; variant < 2; ++variant) {
     const int r2sel = variant ? 4 : 0;
     if (variant && n != 512 && n != 1024) continue;
@@ -75,7 +76,7 @@ inline std::vector<float2> twiddle_tables(int n) {
     for (int pass = 0; pass < 2 && n / ns > 1; ++pass) {
       const int r = pass == 0 ? second_radix_rt(n, r2sel) : n / ns;
       for (int f = 1; f < r; ++f)
-        for (int k = 0; k < ns; ++k) *p++ = phasor(-static_cast<double>(f * k) / (static_cast<double>(ns) * r));
+        for (int k = 0; k < ns; ++k) *p++ = root[f * k * (n / (ns * r))];
       ns *= r;
     }
   }
