@@ -42,11 +42,15 @@ class _Loss(torch.autograd.Function):
         if torch.is_grad_enabled():  # create_graph: a gradient that can be differentiated again
             return torch.autograd.grad(_loss_ops(u_out, i_vac, aperture), u_out, grad_loss, create_graph=True) + \
                 (None, None)
+        # batched cotangents (vmap over the backward pass) have no memory of their own, and a
+        # dual one has a tangent to carry: the kernel then takes 1, and tensor operations the rest
+        direct = torch._C._has_storage(grad_loss) and \
+            torch.autograd.forward_ad.unpack_dual(grad_loss).tangent is None
+        unit = grad_loss.resolve_neg() if direct else torch.ones((), dtype=torch.float32, device=u_out.device)
         grad_u = torch.empty_like(u_out)
         B.receiver_loss_backward(i_vac.numel(), u_out.shape[0], api._ptr(u_out), api._ptr(i_vac), api._ptr(aperture),
-                                 api._ptr(mean), api._ptr(sums), api._ptr(grad_loss.resolve_neg()), api._ptr(grad_u),
-                                 api._stream())
-        return grad_u, None, None
+                                 api._ptr(mean), api._ptr(sums), api._ptr(unit), api._ptr(grad_u), api._stream())
+        return grad_u if direct else grad_u * grad_loss, None, None
 
 
 def _fused(u_out, i_vac, aperture):

@@ -1,0 +1,55 @@
+"""The training loss's backward pass as autograd may call it, against the same
+formula in 64-bit tensor operations: cotangents batched by vmap or carrying a
+tangent.  FP32 intensities carry 2^-23 relative, fluctuations of order one:
+1e-5."""
+import pytest
+import torch
+
+from gpu_helpers import rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def d2nn(gpu_lib):
+    from paper_2604_07248_amd import d2nn as m
+    return m
+
+
+def _inputs(batch=5, n=32, seed=0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    u = torch.randn((batch, n, n), generator=g, device="cuda", dtype=torch.complex64)
+    x = torch.linspace(-1, 1, n, device="cuda")[:, None] ** 2 + torch.linspace(-1, 1, n, device="cuda")[None, :] ** 2
+    return u * torch.exp(-x), torch.exp(-2.2 * x), (x <= 0.6).float()
+
+
+def _reference(d2nn, u, iv, ap):
+    v = u.detach().to(torch.complex128).requires_grad_()
+    return torch.autograd.grad(d2nn._loss_ops(v, iv.double(), ap.double()), v)[0]
+
+
+def test_batched_cotangents(d2nn):
+    u, iv, ap = _inputs()
+    u.requires_grad_()
+    assert d2nn._fused(u, iv, ap)
+    many = torch.tensor([1.0, -2.0, 0.5], device="cuda")
+    want = many.double()[:, None, None, None] * _reference(d2nn, u, iv, ap)
+    got = [torch.autograd.grad(d2nn.loss_fn(u, iv, ap), u, many, is_grads_batched=True)[0]]
+    loss = d2nn.loss_fn(u, iv, ap)
+    got.append(torch.func.vmap(lambda g: torch.autograd.grad(loss, u, g, retain_graph=True)[0])(many))
+    for g in got:
+        assert rel_l2(g.cpu().numpy(), want.cpu().numpy()) < 1e-5
+    jac = torch.autograd.functional.jacobian(lambda v: d2nn.loss_fn(v, iv, ap), u.detach(), vectorize=True)
+    assert rel_l2(jac.cpu().numpy(), want[0].cpu().numpy()) < 1e-5
+
+
+def test_dual_cotangent(d2nn):
+    u, iv, ap = _inputs(seed=1)
+    u.requires_grad_()
+    want = _reference(d2nn, u, iv, ap).cpu().numpy()
+    with torch.autograd.forward_ad.dual_level():
+        g = torch.autograd.forward_ad.make_dual(torch.tensor(2.0, device="cuda"), torch.tensor(-3.0, device="cuda"))
+        (grad,) = torch.autograd.grad(d2nn.loss_fn(u, iv, ap), u, g)
+        value, tangent = torch.autograd.forward_ad.unpack_dual(grad)
+    assert rel_l2(value.cpu().numpy(), 2 * want) < 1e-5
+    assert rel_l2(tangent.cpu().numpy(), -3 * want) < 1e-5
