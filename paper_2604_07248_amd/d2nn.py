@@ -68,7 +68,8 @@ def _fused(u_out, i_vac, aperture):
     if torch.overrides._get_current_function_mode_stack() or torch.utils._python_dispatch._get_current_dispatch_mode():
         return False
     return (u_out.is_cuda and u_out.device.index == torch.cuda.current_device() and u_out.dtype == torch.complex64
-            and u_out.dim() == 3 and u_out.is_contiguous() and not u_out.is_conj() and 0 < u_out.numel()
+            and u_out.dim() == 3 and u_out.is_contiguous() and not u_out.is_conj() and not u_out.is_neg()
+            and 0 < u_out.numel()
             and u_out.shape[0] <= 1 << 19
             and all(t.device == u_out.device and t.dtype == torch.float32 and t.shape == u_out.shape[1:]
                     and t.is_contiguous() and not t.is_neg() and not t.requires_grad

@@ -1,6 +1,6 @@
 """The training loss's backward pass as autograd may call it, against the same
 formula in 64-bit tensor operations: cotangents batched by vmap or carrying a
-tangent.  FP32 intensities carry 2^-23 relative, fluctuations of order one:
+tangent, negated fields.  FP32 intensities carry 2^-23 relative, fluctuations of order one:
 1e-5."""
 import pytest
 import torch
@@ -53,3 +53,12 @@ def test_dual_cotangent(d2nn):
         value, tangent = torch.autograd.forward_ad.unpack_dual(grad)
     assert rel_l2(value.cpu().numpy(), 2 * want) < 1e-5
     assert rel_l2(tangent.cpu().numpy(), -3 * want) < 1e-5
+
+
+def test_negated_fields(d2nn):
+    """A lazily negated view keeps its sign in the gradient."""
+    u, iv, ap = _inputs(seed=2)
+    v = torch._neg_view(u).requires_grad_()
+    assert v.is_neg() and not d2nn._fused(v, iv, ap)
+    (grad,) = torch.autograd.grad(d2nn.loss_fn(v, iv, ap), v)
+    assert rel_l2(grad.cpu().numpy(), _reference(d2nn, -u, iv, ap).cpu().numpy()) < 1e-5
