@@ -47,33 +47,47 @@ class _Loss(torch.autograd.Function):
         direct = torch._C._has_storage(grad_loss) and \
             torch.autograd.forward_ad.unpack_dual(grad_loss).tangent is None
         unit = grad_loss.resolve_neg() if direct else torch.ones((), dtype=torch.float32, device=u_out.device)
-        grad_u = torch.empty_like(u_out)
-        B.receiver_loss_backward(i_vac.numel(), u_out.shape[0], api._ptr(u_out), api._ptr(i_vac), api._ptr(aperture),
-                                 api._ptr(mean), api._ptr(sums), api._ptr(unit), api._ptr(grad_u), api._stream())
-        return grad_u if direct else grad_u * grad_loss, None, None
+        if _readable(u_out, i_vac, aperture) and _is(mean, i_vac, torch.float32, i_vac.shape) and \
+                _is(sums, i_vac, torch.float64, (_Loss.SUMS,)):
+            grad_u = torch.empty_like(u_out)
+            B.receiver_loss_backward(i_vac.numel(), u_out.shape[0], api._ptr(u_out), api._ptr(i_vac),
+                                     api._ptr(aperture), api._ptr(mean), api._ptr(sums), api._ptr(unit),
+                                     api._ptr(grad_u), api._stream())
+            if direct:
+                return grad_u, None, None
+        else:  # saved-tensor hooks may hand back other types and layouts than were saved
+            with torch.enable_grad():
+                u_again = u_out.detach().requires_grad_()
+                (grad_u,) = torch.autograd.grad(_loss_ops(u_again, i_vac, aperture), u_again)
+        return grad_u * grad_loss, None, None
+
+
+def _is(t, like, dtype, shape):
+    """A plain contiguous tensor of this type and shape on the device of `like`."""
+    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == like.device and t.dtype == dtype
+            and t.shape == tuple(shape) and t.is_contiguous() and not t.is_neg() and not t.is_conj()
+            and torch.autograd.forward_ad.unpack_dual(t).tangent is None)
+
+
+def _readable(u_out, i_vac, aperture):
+    """Whether the library's kernels can read these: contiguous complex64 fields
+    and float32 planes on the current GPU."""
+    return (type(u_out) in (torch.Tensor, torch.nn.Parameter) and u_out.is_cuda
+            and u_out.device.index == torch.cuda.current_device() and u_out.dim() == 3 and 0 < u_out.numel()
+            and u_out.shape[0] <= 1 << 19 and _is(u_out, u_out, torch.complex64, u_out.shape)
+            and all(_is(t, u_out, torch.float32, u_out.shape[1:]) for t in (i_vac, aperture)))
 
 
 def _fused(u_out, i_vac, aperture):
     """Whether the library's kernels can stand in for the tensor operations:
-    contiguous complex64 fields and float32 planes on the current GPU, no
-    gradient asked for the planes, and nobody watching the operations (function
-    transforms, forward-mode derivatives, tracing, compilation, tensor subclasses)."""
-    planes = (i_vac, aperture)
-    if any(type(t) not in (torch.Tensor, torch.nn.Parameter) for t in (u_out,) + planes):
-        return False
+    inputs they can read, no gradient asked for the planes, and nobody watching
+    the operations (function transforms, forward-mode derivatives, tracing,
+    compilation, tensor subclasses)."""
     if torch._C._are_functorch_transforms_active() or torch.jit.is_tracing() or torch.compiler.is_compiling():
-        return False
-    if torch.autograd.forward_ad.unpack_dual(u_out).tangent is not None:
         return False
     if torch.overrides._get_current_function_mode_stack() or torch.utils._python_dispatch._get_current_dispatch_mode():
         return False
-    return (u_out.is_cuda and u_out.device.index == torch.cuda.current_device() and u_out.dtype == torch.complex64
-            and u_out.dim() == 3 and u_out.is_contiguous() and not u_out.is_conj() and not u_out.is_neg()
-            and 0 < u_out.numel()
-            and u_out.shape[0] <= 1 << 19
-            and all(t.device == u_out.device and t.dtype == torch.float32 and t.shape == u_out.shape[1:]
-                    and t.is_contiguous() and not t.is_neg() and not t.requires_grad
-                    and torch.autograd.forward_ad.unpack_dual(t).tangent is None for t in planes))
+    return _readable(u_out, i_vac, aperture) and not (i_vac.requires_grad or aperture.requires_grad)
 
 
 def loss_fn(u_out, i_vac, aperture):

@@ -1,6 +1,7 @@
 """The training loss's backward pass as autograd may call it, against the same
 formula in 64-bit tensor operations: cotangents batched by vmap or carrying a
-tangent, negated fields.  FP32 intensities carry 2^-23 relative, fluctuations of order one:
+tangent, negated fields, saved-tensor hooks that hand back other layouts and
+types.  FP32 intensities carry 2^-23 relative, fluctuations of order one:
 1e-5."""
 import pytest
 import torch
@@ -62,3 +63,27 @@ def test_negated_fields(d2nn):
     assert v.is_neg() and not d2nn._fused(v, iv, ap)
     (grad,) = torch.autograd.grad(d2nn.loss_fn(v, iv, ap), v)
     assert rel_l2(grad.cpu().numpy(), _reference(d2nn, -u, iv, ap).cpu().numpy()) < 1e-5
+
+
+HOOKS = {
+    "strided": (lambda t: t.transpose(0, -1).contiguous(), lambda t: t.transpose(0, -1)),
+    "wide": (lambda t: t.to(torch.complex128 if t.is_complex() else torch.float64), lambda t: t),
+    "offloaded": (lambda t: t.cpu(), lambda t: t.cuda()),
+}
+
+
+@pytest.mark.parametrize("kind", list(HOOKS))
+def test_saved_tensor_hooks(d2nn, kind):
+    """What a hook unpacks need not be laid out as it was saved."""
+    u, iv, ap = _inputs(seed=3)
+    u.requires_grad_()
+    assert d2nn._fused(u, iv, ap)
+    many = torch.tensor([3.0, -1.0], device="cuda")
+    with torch.autograd.graph.saved_tensors_hooks(*HOOKS[kind]):
+        loss = d2nn.loss_fn(u, iv, ap)
+    (grad,) = torch.autograd.grad(3.0 * loss, u, retain_graph=True)
+    (both,) = torch.autograd.grad(loss, u, many, is_grads_batched=True)
+    want = _reference(d2nn, u, iv, ap).cpu().numpy()
+    assert grad.dtype == torch.complex64
+    assert rel_l2(grad.cpu().numpy(), 3.0 * want) < 1e-5
+    assert rel_l2(both.cpu().numpy(), many.cpu().numpy()[:, None, None, None] * want) < 1e-5
