@@ -297,29 +297,30 @@ constexpr int kLossChunk = 16;
 // with S0..S3 the four sums (the mean's share of the variance's derivative is
 // zero), and dL/du = 2 u dL/dI.
 __global__ __launch_bounds__(kLossThreads) void loss_grad_kernel(LossArgs a) {
-  const int64_t p = static_cast<int64_t>(blockIdx.x) * kLossThreads + threadIdx.x;
-  if (p >= a.pixels) return;
   const double inv = 1.0 / static_cast<double>(a.batch), g = 2.0 * *a.grad_loss;
   const double s0 = a.sums[0], s1 = a.sums[1], s3 = a.sums[3];
-  const double m1 = a.mean[p], ap = a.aperture[p], iv = a.i_vac[p];
-  const float mean = a.mean[p];
-  const float slope = static_cast<float>(g * 2.0 * ap * inv / s1);
-  const float level = static_cast<float>(g * inv * (-2.0 * s0 * ap * m1 / (s1 * s1) + 2.0 * (m1 - iv) / s3));
   const int64_t b0 = static_cast<int64_t>(blockIdx.y) * kLossChunk;
-  if (b0 + kLossChunk <= a.batch) {
-    float2 u[kLossChunk];
+  const int64_t stride = static_cast<int64_t>(gridDim.x) * kLossThreads;
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * kLossThreads + threadIdx.x; p < a.pixels; p += stride) {
+    const double m1 = a.mean[p], ap = a.aperture[p], iv = a.i_vac[p];
+    const float mean = a.mean[p];
+    const float slope = static_cast<float>(g * 2.0 * ap * inv / s1);
+    const float level = static_cast<float>(g * inv * (-2.0 * s0 * ap * m1 / (s1 * s1) + 2.0 * (m1 - iv) / s3));
+    if (b0 + kLossChunk <= a.batch) {
+      float2 u[kLossChunk];
 #pragma unroll
-    for (int q = 0; q < kLossChunk; ++q) u[q] = ld_s<true>(a.u + (b0 + q) * a.pixels + p);
+      for (int q = 0; q < kLossChunk; ++q) u[q] = ld_s<true>(a.u + (b0 + q) * a.pixels + p);
 #pragma unroll
-    for (int q = 0; q < kLossChunk; ++q) {
-      const float w = slope * (u[q].x * u[q].x + u[q].y * u[q].y - mean) + level;
-      a.grad_u[(b0 + q) * a.pixels + p] = c_scale(u[q], w);
-    }
-  } else {
-    for (int64_t b = b0; b < a.batch; ++b) {
-      const float2 u = a.u[b * a.pixels + p];
-      const float w = slope * (u.x * u.x + u.y * u.y - mean) + level;
-      a.grad_u[b * a.pixels + p] = c_scale(u, w);
+      for (int q = 0; q < kLossChunk; ++q) {
+        const float w = slope * (u[q].x * u[q].x + u[q].y * u[q].y - mean) + level;
+        a.grad_u[(b0 + q) * a.pixels + p] = c_scale(u[q], w);
+      }
+    } else {
+      for (int64_t b = b0; b < a.batch; ++b) {
+        const float2 u = a.u[b * a.pixels + p];
+        const float w = slope * (u.x * u.x + u.y * u.y - mean) + level;
+        a.grad_u[b * a.pixels + p] = c_scale(u, w);
+      }
     }
   }
 }
@@ -383,8 +384,16 @@ hipError_t launch_loss(const LossArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Blocks of the adjoint along the pixels: one pixel a thread while a launch
+// allows that many threads in x (fewer than 2^32), more beyond.
+constexpr int64_t loss_grad_blocks(int64_t pixels) {
+  const int64_t b = (pixels + kLossThreads - 1) / kLossThreads, most = (int64_t(1) << 32) / kLossThreads - 1;
+  return b < most ? b : most;
+}
+static_assert(loss_grad_blocks(int64_t(1) << 32) * kLossThreads < int64_t(1) << 32, "one launch covers 2^32 pixels");
+
 hipError_t launch_loss_grad(const LossArgs& a, hipStream_t s) {
-  const dim3 grid(static_cast<uint32_t>((a.pixels + kLossThreads - 1) / kLossThreads),
+  const dim3 grid(static_cast<uint32_t>(loss_grad_blocks(a.pixels)),
                   static_cast<uint32_t>((a.batch + kLossChunk - 1) / kLossChunk));
   hipLaunchKernelGGL(loss_grad_kernel, grid, dim3(kLossThreads), 0, s, a);
   return hipGetLastError();
