@@ -169,8 +169,9 @@ turpy_status turpy_propagate(turpy_plan* plan, uint64_t seed, int64_t t, const v
  * (screen planes, subharmonic coefficients, the shared-source plane) lives in
  * a fixed 64 MiB device array of the library, one per GPU, held until the
  * process ends; the array's address is looked up by turpy_plan_create.  Other
- * arguments and results as turpy_propagate (bit-identical).  A plan whose
- * turpy_workspace_size(TURPY_OP_PROPAGATE) exceeds 64 MiB is refused with
+ * arguments and results as turpy_propagate (bit-identical).  A plan that needs
+ * more than 64 MiB with one screen at a time in it (ceil(R/2) N^2 complex64
+ * words, beside the coefficients and the plane) is refused with
  * TURPY_E_WORKSPACE (N = 1024: at most 14 realizations; N = 512: 62).
  * Every call on one GPU shares that GPU's array and leaves its contents
  * behind (no part of it needs to start at zero): calls that overlap on one

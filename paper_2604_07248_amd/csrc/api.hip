@@ -292,8 +292,7 @@ void keep_screens(const turpy_plan* pl, void* checkpoints, int32_t src, Ws* w) {
   const size_t plane = static_cast<size_t>(pl->n) * pl->n;
   w->screens = static_cast<float2*>(checkpoints) + static_cast<size_t>(pl->R) * pl->M * plane;
   w->screen_stride = static_cast<size_t>(pl->P) * plane;
-  w->batch = std::max(1, std::min({pl->M, kSynthScreens,
-                                   static_cast<int>(pl->scratch_bytes() / (w->screen_stride * sizeof(float2)))}));
+  w->batch = screens_per_launch(pl, w->screen_stride, pl->scratch_bytes());
   w->solo = false;  // full planes, as the buffer's layout says
 }
 
@@ -475,10 +474,11 @@ turpy_status turpy_screen_generate(turpy_plan* pl, uint64_t seed, int64_t t, flo
 namespace {
 
 // turpy_propagate; with `ev`, every screen's synthesis first takes the AR step
-// of its stored spectra (turpy_evolve_propagate).
+// of its stored spectra (turpy_evolve_propagate).  `scratch`: bytes of the
+// workspace for the screens' column halves (0: the plan's own choice).
 turpy_status propagate_impl(turpy_plan* pl, uint64_t seed, int64_t t, const void* u_in, int64_t u_in_stride,
                             int32_t src, const void* screens_or_spectra, void* u_out, void* checkpoints, void* ws,
-                            size_t ws_bytes, void* stream, const EvolveStep* ev) {
+                            size_t ws_bytes, void* stream, const EvolveStep* ev, size_t scratch = 0) {
   if (!pl || !u_in || !u_out) return fail(TURPY_E_INVALID, "propagate: NULL argument");
   if (turpy_status s_ = check_t(t)) return s_;
   if (turpy_status s_ = check_device(pl)) return s_;
@@ -488,11 +488,12 @@ turpy_status propagate_impl(turpy_plan* pl, uint64_t seed, int64_t t, const void
     return fail(TURPY_E_INVALID, "propagate: u_in_stride must be 0 or N*N");
   if (u_in_stride == 0 && u_in == u_out && pl->R > 1)
     return fail(TURPY_E_INVALID, "propagate: a shared source cannot alias u_out");
-  if (!ws || ws_bytes < pl->ws_forward())
-    return fail(TURPY_E_WORKSPACE, "propagate: workspace %zu < %zu bytes", ws_bytes, pl->ws_forward());
+  if (scratch == 0) scratch = pl->scratch_bytes();
+  if (!ws || ws_bytes < pl->ws_forward(scratch))
+    return fail(TURPY_E_WORKSPACE, "propagate: workspace %zu < %zu bytes", ws_bytes, pl->ws_forward(scratch));
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (turpy_status s_ = check_capture(pl, st, "propagate")) return s_;
-  Ws w = carve(pl, ws, src);
+  Ws w = carve(pl, ws, src, scratch);
   keep_screens(pl, checkpoints, src, &w);
   const int n = pl->n, M = pl->M;
   const float inv_n = 1.0f / n;
@@ -643,15 +644,18 @@ turpy_status turpy_propagate_static(turpy_plan* pl, uint64_t seed, int64_t t, co
                                     void* checkpoints, void* stream) {
   if (!pl) return fail(TURPY_E_INVALID, "propagate_static: NULL plan");
   if (turpy_status s_ = check_device(pl)) return s_;
-  const size_t need = pl->ws_forward();
+  // one screen's planes have to fit; the launches then take as many screens as do
+  const size_t one = static_cast<size_t>(pl->P) * pl->plane_bytes();
+  const size_t need = pl->ws_forward(one);
   if (need > kStaticScratchBytes)
     return fail(TURPY_E_WORKSPACE,
                 "propagate_static: the plan needs %zu bytes of scratch, beyond the %zu of the static array "
                 "(use turpy_propagate with a workspace)", need, kStaticScratchBytes);
   void* ptr = static_scratch(pl->device);
   if (!ptr) return fail(TURPY_E_INVALID, "propagate_static: no scratch address for device %d", pl->device);
-  return turpy_propagate(pl, seed, t, u_in, u_in_stride, src, screens_or_spectra, u_out, checkpoints, ptr,
-                         kStaticScratchBytes, stream);
+  const size_t room = kStaticScratchBytes - pl->ws_forward(0);
+  return propagate_impl(pl, seed, t, u_in, u_in_stride, src, screens_or_spectra, u_out, checkpoints, ptr,
+                        kStaticScratchBytes, stream, nullptr, std::min(pl->scratch_bytes(), room / one * one));
 }
 
 static turpy_status backward_checkpointed(turpy_plan* pl, uint64_t seed, int64_t t, const void* grad_u_out,

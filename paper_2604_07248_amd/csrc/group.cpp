@@ -75,7 +75,7 @@ std::string group_key(const turpy_plan* pl) {
 }
 
 size_t group_member_workspace(const turpy_plan* pl) {
-  return align_up(static_cast<size_t>(pl->P) * pl->plane_bytes()) + pl->off_src() - pl->off_sh();
+  return align_up(static_cast<size_t>(pl->P) * pl->plane_bytes()) + pl->sh_bytes();
 }
 
 size_t group_workspace(const Group* g) { return g->ws_bytes; }

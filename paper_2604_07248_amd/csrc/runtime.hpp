@@ -179,11 +179,15 @@ struct turpy_plan {
     const size_t all = one * static_cast<size_t>(M > 0 ? M : 1);
     return std::max(one, std::min(all, turpy::kBatchScratch / one * one));
   }
-  size_t off_sh() const { return turpy::align_up(scratch_bytes()); }
-  size_t off_src() const {
-    return off_sh() + turpy::align_up(sh_levels > 0 ? static_cast<size_t>(P) * (M > 0 ? M : 1) * 32 * sizeof(float2) : 0);
+  size_t sh_bytes() const {
+    return turpy::align_up(sh_levels > 0 ? static_cast<size_t>(P) * (M > 0 ? M : 1) * 32 * sizeof(float2) : 0);
   }
-  size_t off_gbuf() const { return off_src() + turpy::align_up(plane_bytes()); }
+  // the forward pass's workspace with this much scratch: after it the
+  // subharmonic coefficients and the shared-source plane
+  size_t ws_forward(size_t scratch) const {
+    return turpy::align_up(scratch) + sh_bytes() + turpy::align_up(plane_bytes());
+  }
+  size_t off_gbuf() const { return ws_forward(scratch_bytes()); }
   size_t ws_forward() const { return off_gbuf(); }
   size_t ws_backward() const { return off_gbuf() + turpy::align_up(static_cast<size_t>(R) * plane_bytes()); }
   // reversible adjoint: also the rebuilt forward field and its value at the current screen
@@ -216,18 +220,25 @@ struct Ws {
   }
 };
 
+// Screens one synthesis launch covers, `stride` elements apart in this much scratch.
+inline int screens_per_launch(const turpy_plan* pl, size_t stride, size_t scratch) {
+  return std::max(1, std::min({pl->M, kSynthScreens, static_cast<int>(scratch / (stride * sizeof(float2)))}));
+}
+
 // For a call that takes its screens from `src`: synthesised screens of a
 // single realization are held two real rows to a complex one.
-inline Ws carve(const turpy_plan* pl, void* ws, int32_t src) {
+inline Ws carve(const turpy_plan* pl, void* ws, int32_t src, size_t scratch) {
   char* b = static_cast<char*>(ws);
-  Ws w{reinterpret_cast<float2*>(b), reinterpret_cast<float2*>(b + pl->off_sh()),
-       reinterpret_cast<float2*>(b + pl->off_src()), reinterpret_cast<float2*>(b + pl->off_gbuf())};
+  char* sh = b + align_up(scratch);
+  char* source = sh + pl->sh_bytes();
+  Ws w{reinterpret_cast<float2*>(b), reinterpret_cast<float2*>(sh), reinterpret_cast<float2*>(source),
+       reinterpret_cast<float2*>(source + align_up(pl->plane_bytes()))};
   w.solo = src == TURPY_SCREENS_SYNTH && pl->solo();
   w.screen_stride = static_cast<size_t>(pl->P) * pl->n * pl->n / (w.solo ? 2 : 1);
-  w.batch = std::max(1, std::min({pl->M, kSynthScreens,
-                                  static_cast<int>(pl->scratch_bytes() / (w.screen_stride * sizeof(float2)))}));
+  w.batch = screens_per_launch(pl, w.screen_stride, scratch);
   return w;
 }
+inline Ws carve(const turpy_plan* pl, void* ws, int32_t src) { return carve(pl, ws, src, pl->scratch_bytes()); }
 
 inline void key_of(uint64_t seed, uint32_t* k0, uint32_t* k1) {
   *k0 = static_cast<uint32_t>(seed & 0xFFFFFFFFu);

@@ -74,7 +74,8 @@ def _readable(u_out, i_vac, aperture):
     and float32 planes on the current GPU, within the sizes they take."""
     return (type(u_out) in (torch.Tensor, torch.nn.Parameter) and u_out.is_cuda
             and u_out.device.index == torch.cuda.current_device() and u_out.dim() == 3 and 0 < u_out.numel()
-            and u_out.shape[0] <= 1 << 19 and u_out.numel() <= u_out.shape[0] << 32 and _is(u_out, u_out, torch.complex64, u_out.shape)
+            and u_out.shape[0] <= 1 << 19 and u_out.numel() <= u_out.shape[0] << 32
+            and _is(u_out, u_out, torch.complex64, u_out.shape)
             and all(_is(t, u_out, torch.float32, u_out.shape[1:]) for t in (i_vac, aperture)))
 
 
