@@ -293,7 +293,6 @@ void keep_screens(const turpy_plan* pl, void* checkpoints, int32_t src, Ws* w) {
   w->screens = static_cast<float2*>(checkpoints) + static_cast<size_t>(pl->R) * pl->M * plane;
   w->screen_stride = static_cast<size_t>(pl->P) * plane;
   w->batch = screens_per_launch(pl, w->screen_stride, pl->scratch_bytes());
-  w->solo = false;  // full planes, as the buffer's layout says
 }
 
 turpy_status check_t(int64_t t) {

@@ -171,7 +171,10 @@ struct turpy_plan {
   bool screen_ck = false;        // TURPY_SCREEN_CHECKPOINTS: checkpoints keep the screens' column halves
   std::string arch;              // device architecture (tuning-cache key)
 
-  bool solo() const { return R == 1 && turpy::solo_fits(n); }
+  // A single realization's screens are synthesised as real ones (SynthArgs::solo).
+  // Not on a plan that keeps its screens with the checkpoints, whose layout is full
+  // planes: its calls with and without checkpoints then give the same bits.
+  bool solo() const { return R == 1 && !screen_ck && turpy::solo_fits(n); }
   size_t plane_bytes() const { return static_cast<size_t>(n) * n * sizeof(float2); }
   // scratch: the column halves of as many screens as fit kBatchScratch, at least one
   size_t scratch_bytes() const {
