@@ -490,9 +490,12 @@ turpy_status turpy_place_screens(const turpy_cn2_profile* profile, double length
  *    3 is the default, 2 and 4 are built for N >= 256 (bit-identical results).
  * A plan starts from the built-in choices (measured on MI355X), or from the
  * process-wide cache when it holds an entry for the plan's key:
- *   (device architecture, kernel, N, batch class = bit length of the number
- *    of planes one launch covers: R for the column pass, ceil(R/2) for the
- *    synthesis and the row passes).
+ *   (device architecture, kernel, N, batch class).  The batch class is the bit
+ *   length of R for the column pass and of ceil(R/2) for the row passes and for
+ *   the synthesis where one launch fills the chip; 32 + the bit length of the
+ *   planes of a launch (ceil(R/2) times the screens it covers) for a synthesis
+ *   that does not; and 48 + the bit length of the screens of a launch for the
+ *   synthesis of a single realization, which is another kernel.
  * ------------------------------------------------------------------------- */
 typedef enum {
   TURPY_TUNE_COL_FRESNEL = 0,   /* column pass, Fresnel transfer function               */
@@ -512,7 +515,7 @@ typedef struct turpy_tune_entry {
   char arch[32];                /* device architecture, e.g. "gfx950" (NUL-terminated)             */
   int32_t kernel;               /* turpy_tune_kernel                                                */
   int32_t n;                    /* grid size                                                        */
-  int32_t batch_class;          /* bit length of the planes per launch                              */
+  int32_t batch_class;          /* what one launch covers (above)                                   */
   int32_t width;                /* columns per block (4, 8, 16); 0 for the row kernels              */
   int32_t radix;                /* second-pass radix (0: default plan); 0 for the row kernels       */
   int32_t waves;                /* occupancy hint of the row kernels (2, 3, 4); 0 for the others    */
@@ -532,8 +535,9 @@ typedef struct turpy_launch_config {
 
 /* Time every launch configuration of the plan's column pass (its
  * transfer-function kind, distance 0, all R planes in place), and, when the
- * plan has screens, of its synthesis (all ceil(R/2) scratch planes; once
- * plain and once with the AR step fused, on workspace planes as the state)
+ * plan has screens, of its synthesis (a call's first launch, with as many
+ * screens as it covers; once plain and once with the AR step fused, on
+ * workspace planes as the state)
  * and of its forward and adjoint row passes for screen 0 (workspace planes), with
  * HIP events on `stream`, and keep the fastest of each in the plan and in the
  * cache.  A key already in the cache is applied without measuring unless

@@ -289,10 +289,7 @@ namespace {
 // there and the adjoint reads them instead of synthesising them again.
 void keep_screens(const turpy_plan* pl, void* checkpoints, int32_t src, Ws* w) {
   if (!pl->screen_ck || !checkpoints || src == TURPY_SCREENS_MATERIALIZED || pl->M == 0) return;
-  const size_t plane = static_cast<size_t>(pl->n) * pl->n;
-  w->screens = static_cast<float2*>(checkpoints) + static_cast<size_t>(pl->R) * pl->M * plane;
-  w->screen_stride = static_cast<size_t>(pl->P) * plane;
-  w->batch = screens_per_launch(pl, w->screen_stride, pl->scratch_bytes());
+  w->screens = static_cast<float2*>(checkpoints) + static_cast<size_t>(pl->R) * pl->M * pl->n * pl->n;
 }
 
 turpy_status check_t(int64_t t) {
@@ -1302,10 +1299,29 @@ int col_kernel_id(const turpy_plan* pl) {
   return pl->d_as ? TURPY_TUNE_COL_AS_TABLE : TURPY_TUNE_COL_ANGULAR;
 }
 
+// Batch classes of the synthesis.  A launch that has a strip of the built-in
+// width for every CU is classed by its pairs.  One that has not is classed by
+// all its planes, ceil(R/2) for each screen it covers: there the best strip
+// depends on how many there are (AR step at n = 1024: 16 columns 177 us and 4
+// columns 240 on 64 planes, 23.0 and 15.9 on one).  A single realization's
+// screens have a kernel of their own.
+constexpr int kFewPlanes = 32, kSolo = 48;
+
+int synth_class(const turpy_plan* pl, int32_t src, int widest) {
+  const int screens = screens_per_launch(pl, src);
+  if (src == TURPY_SCREENS_SYNTH && pl->solo()) return kSolo + bit_length(screens);
+  const int64_t planes = pl->P * screens;
+  return pl->n / widest * planes >= kFillBlocks ? bit_length(pl->P) : kFewPlanes + bit_length(planes);
+}
+
 TuneKey col_key(const turpy_plan* pl) { return TuneKey{pl->arch, col_kernel_id(pl), pl->n, bit_length(pl->R)}; }
-TuneKey synth_key(const turpy_plan* pl) { return TuneKey{pl->arch, TURPY_TUNE_SYNTH, pl->n, bit_length(pl->P)}; }
+TuneKey synth_key(const turpy_plan* pl) {
+  return TuneKey{pl->arch, TURPY_TUNE_SYNTH, pl->n, synth_class(pl, TURPY_SCREENS_SYNTH, widest_synth(pl->n))};
+}
 TuneKey row_key(const turpy_plan* pl, int kernel) { return TuneKey{pl->arch, kernel, pl->n, bit_length(pl->P)}; }
-TuneKey ar_key(const turpy_plan* pl) { return TuneKey{pl->arch, TURPY_TUNE_SYNTH_AR, pl->n, bit_length(pl->P)}; }
+TuneKey ar_key(const turpy_plan* pl) {
+  return TuneKey{pl->arch, TURPY_TUNE_SYNTH_AR, pl->n, synth_class(pl, TURPY_SCREENS_SPECTRA, widest_ar(pl->n))};
+}
 
 bool cached(const TuneKey& k, turpy_tune_entry* e) {
   std::lock_guard<std::mutex> lock(g_tune_mu);
@@ -1424,10 +1440,12 @@ std::vector<LaunchChoice> wave_choices(int n) {
 }  // namespace
 
 std::string turpy::tune_signature(const turpy_plan* pl) {
-  const TuneKey c = col_key(pl), s = synth_key(pl);
+  const TuneKey c = col_key(pl);
+  const bool screens = pl->M > 0;
   char buf[96];
-  std::snprintf(buf, sizeof(buf), "%s/%d/%d/%d/%d/%d", c.arch.c_str(), c.kernel, c.n, c.batch_class,
-                pl->M > 0 ? s.batch_class : 0, pl->M > 0 ? 1 : 0);
+  std::snprintf(buf, sizeof(buf), "%s/%d/%d/%d/%d/%d/%d", c.arch.c_str(), c.kernel, c.n, c.batch_class,
+                screens ? synth_key(pl).batch_class : 0, screens ? ar_key(pl).batch_class : 0,
+                screens ? row_key(pl, TURPY_TUNE_ROW_FWD).batch_class : 0);
   return buf;
 }
 
@@ -1469,9 +1487,10 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
       return s;
   }
   if (need_synth) {
-    SynthArgs a = synth_args(pl, 0, 0, 0, 1, nullptr, wsp);
+    // the first launch of a call: as many screens as one covers
+    SynthArgs a = synth_args(pl, 0, 0, 0, wsp.batch, nullptr, wsp);
     a.t_dev = nullptr;
-    if (turpy_status s = tune_key(sk, strip_choices(n), {default_synth_width(n, pl->P), 0, 0}, st,
+    if (turpy_status s = tune_key(sk, strip_choices(n), {default_synth_width(n, pl->P * wsp.batch), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
                                     a.width = k.width;
                                     a.radix = k.radix;
@@ -1480,23 +1499,24 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
       return s;
   }
   if (need_ar) {
-    // the AR step of screen 0 on a state of one screen per pair (pair j at
-    // plane j), alternating between two such states (the R-plane buffer and
-    // the buffer after it): as in a step over M screens, the state a launch
-    // reads is not the one the launch before it left in the last-level cache
+    // the AR step of a launch's screens on a state that holds them alone,
+    // alternating between two such states: as in a step over M screens, the
+    // state a launch reads is not the one the launch before it left in the
+    // last-level cache
     const EvolveStep ev{0.99, 0.5, 0.25};
-    float2* second = reinterpret_cast<float2*>(static_cast<char*>(ws) + pl->off_ubuf());
-    SynthArgs a = synth_args(pl, 0, 1, 0, 1, wsp.gbuf, wsp, &ev);
-    a.solo = 0;
+    const Ws wa = carve(pl, ws, TURPY_SCREENS_SPECTRA);
+    const int64_t planes = pl->P * wa.batch;
+    float2* second = wa.gbuf + planes * plane;
+    SynthArgs a = synth_args(pl, 0, 1, 0, wa.batch, wa.gbuf, wa, &ev);
     a.t_dev = nullptr;
-    a.M = 1;
+    a.M = wa.batch;
     bool flip = false;
-    if (turpy_status s = tune_key(ak, strip_choices(n), {default_ar_width(n, pl->P), 0, 0}, st,
+    if (turpy_status s = tune_key(ak, strip_choices(n), {default_ar_width(n, planes), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
                                     a.width = k.width;
                                     a.radix = k.radix;
                                     flip = !flip;
-                                    a.state = flip ? second : wsp.gbuf;
+                                    a.state = flip ? second : wa.gbuf;
                                     return launch_synth(n, a, st);
                                   }))
       return s;

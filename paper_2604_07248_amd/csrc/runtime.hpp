@@ -196,8 +196,9 @@ struct turpy_plan {
   // reversible adjoint: also the rebuilt forward field and its value at the current screen
   size_t off_ubuf() const { return ws_backward(); }
   size_t ws_reversible() const { return ws_backward() + 2 * turpy::align_up(static_cast<size_t>(R) * plane_bytes()); }
-  // tuning: the scratch planes (synthesis) and the R-plane buffer (column pass)
-  size_t ws_tune() const { return ws_reversible(); }
+  // tuning: the scratch planes (synthesis) and the R-plane buffers (column and
+  // row passes), or in their place two states of the screens of one AR launch
+  size_t ws_tune() const;
 };
 
 namespace turpy {
@@ -223,13 +224,23 @@ struct Ws {
   }
 };
 
-// Screens one synthesis launch covers, `stride` elements apart in this much scratch.
-inline int screens_per_launch(const turpy_plan* pl, size_t stride, size_t scratch) {
-  return std::max(1, std::min({pl->M, kSynthScreens, static_cast<int>(scratch / (stride * sizeof(float2)))}));
+// Elements from one screen's column halves to the next's in the scratch of a
+// call that takes its screens from `src`: synthesised screens of a single
+// realization are held two real rows to a complex one.
+inline size_t screen_stride(const turpy_plan* pl, int32_t src) {
+  const bool solo = src == TURPY_SCREENS_SYNTH && pl->solo();
+  return static_cast<size_t>(pl->P) * pl->n * pl->n / (solo ? 2 : 1);
 }
 
-// For a call that takes its screens from `src`: synthesised screens of a
-// single realization are held two real rows to a complex one.
+// Screens that one synthesis launch of such a call covers.
+inline int screens_per_launch(const turpy_plan* pl, int32_t src, size_t scratch) {
+  const size_t one = screen_stride(pl, src) * sizeof(float2);
+  return std::max(1, std::min({pl->M, kSynthScreens, static_cast<int>(scratch / one)}));
+}
+inline int screens_per_launch(const turpy_plan* pl, int32_t src) {
+  return screens_per_launch(pl, src, pl->scratch_bytes());
+}
+
 inline Ws carve(const turpy_plan* pl, void* ws, int32_t src, size_t scratch) {
   char* b = static_cast<char*>(ws);
   char* sh = b + align_up(scratch);
@@ -237,11 +248,20 @@ inline Ws carve(const turpy_plan* pl, void* ws, int32_t src, size_t scratch) {
   Ws w{reinterpret_cast<float2*>(b), reinterpret_cast<float2*>(sh), reinterpret_cast<float2*>(source),
        reinterpret_cast<float2*>(source + align_up(pl->plane_bytes()))};
   w.solo = src == TURPY_SCREENS_SYNTH && pl->solo();
-  w.screen_stride = static_cast<size_t>(pl->P) * pl->n * pl->n / (w.solo ? 2 : 1);
-  w.batch = screens_per_launch(pl, w.screen_stride, scratch);
+  w.screen_stride = screen_stride(pl, src);
+  w.batch = screens_per_launch(pl, src, scratch);
   return w;
 }
 inline Ws carve(const turpy_plan* pl, void* ws, int32_t src) { return carve(pl, ws, src, pl->scratch_bytes()); }
+
+}  // namespace turpy
+
+inline size_t turpy_plan::ws_tune() const {
+  const size_t state = static_cast<size_t>(P) * turpy::screens_per_launch(this, TURPY_SCREENS_SPECTRA) * plane_bytes();
+  return std::max(ws_reversible(), off_gbuf() + 2 * turpy::align_up(state));
+}
+
+namespace turpy {
 
 inline void key_of(uint64_t seed, uint32_t* k0, uint32_t* k1) {
   *k0 = static_cast<uint32_t>(seed & 0xFFFFFFFFu);
