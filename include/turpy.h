@@ -494,8 +494,9 @@ turpy_status turpy_place_screens(const turpy_cn2_profile* profile, double length
  *   length of R for the column pass and of ceil(R/2) for the row passes and for
  *   the synthesis where one launch fills the chip; 32 + the bit length of the
  *   planes of a launch (ceil(R/2) times the screens it covers) for a synthesis
- *   that does not; and 48 + the bit length of the screens of a launch for the
- *   synthesis of a single realization, which is another kernel.
+ *   that does not; and for a single realization 48 + the bit length of the
+ *   screens of a launch for the synthesis, which is another kernel, and 49 for
+ *   the row passes, which cover half the rows.
  * ------------------------------------------------------------------------- */
 typedef enum {
   TURPY_TUNE_COL_FRESNEL = 0,   /* column pass, Fresnel transfer function               */
@@ -538,7 +539,10 @@ typedef struct turpy_launch_config {
  * plan has screens, of its synthesis (a call's first launch, with as many
  * screens as it covers; once plain and once with the AR step fused, on
  * workspace planes as the state)
- * and of its forward and adjoint row passes for screen 0 (workspace planes), with
+ * and of its forward and adjoint row passes for screen 0 (workspace planes; the
+ * schedules that take the hint, which launches of up to 2^20 pixels of screen
+ * planes at N = 64..1024 are not: nothing is measured where no plan of the
+ * class launches one), with
  * HIP events on `stream`, and keep the fastest of each in the plan and in the
  * cache.  A key already in the cache is applied without measuring unless
  * flags has TURPY_TUNE_FORCE.  Each configuration: one launch, then 3

@@ -1318,7 +1318,15 @@ TuneKey col_key(const turpy_plan* pl) { return TuneKey{pl->arch, col_kernel_id(p
 TuneKey synth_key(const turpy_plan* pl) {
   return TuneKey{pl->arch, TURPY_TUNE_SYNTH, pl->n, synth_class(pl, TURPY_SCREENS_SYNTH, widest_synth(pl->n))};
 }
-TuneKey row_key(const turpy_plan* pl, int kernel) { return TuneKey{pl->arch, kernel, pl->n, bit_length(pl->P)}; }
+// A single realization's row passes cover half the rows.
+TuneKey row_key(const turpy_plan* pl, int kernel) {
+  return TuneKey{pl->arch, kernel, pl->n, pl->solo() ? kSolo + 1 : bit_length(pl->P)};
+}
+// Whether any plan of row_key's class launches a schedule that takes the
+// occupancy hint (the one-worker-per-transform schedule takes none).
+bool row_hint_used(const turpy_plan* pl) {
+  return !trio_takes(pl->n, pl->solo() ? 1 : (int64_t(1) << bit_length(pl->P)) - 1, pl->solo());
+}
 TuneKey ar_key(const turpy_plan* pl) {
   return TuneKey{pl->arch, TURPY_TUNE_SYNTH_AR, pl->n, synth_class(pl, TURPY_SCREENS_SPECTRA, widest_ar(pl->n))};
 }
@@ -1470,8 +1478,9 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
   const bool need_synth = screens && (force || !cached(sk, &e));
   const TuneKey ak = ar_key(pl);
   const bool need_ar = screens && (force || !cached(ak, &e));
-  const bool need_rf = screens && (force || !cached(rf, &e));
-  const bool need_rb = screens && (force || !cached(rb, &e));
+  const bool hint = screens && row_hint_used(pl);
+  const bool need_rf = hint && (force || !cached(rf, &e));
+  const bool need_rb = hint && (force || !cached(rb, &e));
   if (need_col || need_synth || need_ar || need_rf || need_rb)
     TURPY_HIP(hipMemsetAsync(ws, 0, pl->ws_tune(), st), "plan_tune: clear workspace");
   const Ws wsp = carve(pl, ws, TURPY_SCREENS_SYNTH);
@@ -1533,6 +1542,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
     a.out_spectral = 1;
     a.scale = 1.0f / n;
     a.M = 1;
+    a.hinted = 1;  // the choice goes to every plan of the class, also to those above this one's size
     screen_fields(pl, TURPY_SCREENS_SYNTH, nullptr, wsp, 0, &a);
     a.screen = 0;
     if (need_rf) {

@@ -1717,20 +1717,14 @@ constexpr bool row_waves_built(int n, int w) { return w == kRowWaves || (n >= 25
 // (252 such instances at N = 2048 274 -> 213 ms forward).
 template <int N>
 bool solo_forward(const RowArgs& a) {
-  return N > 1024 && a.R == 1 && !a.backward && !a.solo;
+  return N > 1024 && a.R == 1 && !a.backward && !a.solo && !a.hinted;
 }
 
-// The one-worker-per-transform schedule up to 2^20 pixels of scratch planes in a
-// launch, where its shorter chain beats the busier blocks of the others (us
-// with it and without, forward, events around each launch: n = 256, 32
-// realizations 16.6 / 19.6, 64 22.6 / 21.8; n = 512, 8 realizations 18.4 /
-// 21.7, 16 26.2 / 24.4; n = 1024, 2 realizations 20.7 / 22.1, 4 30.0 / 25.6;
-// the adjoint's lines lie at the same sizes or one step above).  The results
-// are the other schedules' bit for bit.
+// The one-worker-per-transform schedule, on the launches trio_takes says.  The
+// results are the other schedules' bit for bit.
 template <int N>
 bool trio_pays(const RowArgs& a, int64_t planes) {
-  return trio_fits(N) && a.screen_mode == ROW_SCRATCH && !a.phase_out &&
-         planes * (a.solo ? N / 2 : N) * N <= (int64_t(1) << 20);
+  return trio_takes(N, planes, a.solo) && a.screen_mode == ROW_SCRATCH && !a.phase_out && !a.hinted;
 }
 
 // The relay kernel for forward passes with synthesised screens and no

@@ -48,6 +48,7 @@ struct RowArgs {
   int screen_count;
   size_t screen_stride;
   int waves;                // occupancy hint of the screen row passes (2, 3, 4; 0: the default)
+  int hinted;               // 1: a schedule that takes the hint, whatever the launch's size (the tuner)
   // One realization with solo scratch (SynthArgs::solo): its rows y and
   // y + N/2 take the places of a pair's two realizations, N/2 rows apiece
   int solo;

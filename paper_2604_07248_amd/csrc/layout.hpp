@@ -91,6 +91,15 @@ constexpr int pair_block() { return 2 * pair_rows<N>() * (N / kE); }
 // Row pass with one worker per transform: a worker is one wave over
 // `trio_rows` rows.
 constexpr bool trio_fits(int n) { return n >= 64 && n <= 1024; }
+// It runs up to 2^20 pixels of scratch planes in a launch (N/2 rows apiece for
+// a single realization), where its shorter chain beats the busier blocks of the
+// other schedules (us with it and without, forward, events around each launch:
+// n = 256, 32 realizations 16.6 / 19.6, 64 22.6 / 21.8; n = 512, 8 realizations
+// 18.4 / 21.7, 16 26.2 / 24.4; n = 1024, 2 realizations 20.7 / 22.1, 4 30.0 /
+// 25.6; the adjoint's lines lie at the same sizes or one step above).
+constexpr bool trio_takes(int n, int64_t planes, bool solo) {
+  return trio_fits(n) && planes * (solo ? n / 2 : n) * n <= (int64_t(1) << 20);
+}
 template <int N>
 constexpr int trio_rows() { return 64 / (N / kE); }
 template <int N>

@@ -1,6 +1,7 @@
 """The tuner against the launches that calls make: the synthesis is timed with
 as many screens as a call's launch covers, and what it chose goes only to plans
-whose launches are alike."""
+whose launches are alike.  The row passes' occupancy hint is timed on the
+schedules that take one."""
 import ctypes
 
 import pytest
@@ -85,3 +86,41 @@ def test_tuning_stays_in_its_workspace(api):
                                         api._stream(), None, None))
         assert bool((ws[size:] == 0xA5).all())
         plan.close()
+
+
+# 64 and 1024, one pair: every launch of the class runs one wave per transform,
+# which takes no hint.  512, 4 pairs do too, but not the 7 of the same class
+@pytest.mark.parametrize("n,r,classes", [(64, 4, []), (1024, 2, []), (256, 1, []), (512, 8, [3]), (512, 16, [4]),
+                                         (2048, 1, [49]), (2048, 2, [1])])
+def test_hints_where_a_launch_takes_one(api, n, r, classes):
+    path = _path(n, r, 2)
+    plan = api.Plan(path)
+    u0 = torch.from_numpy(workloads.seeded_field((n, n), 9)).cuda()
+    ref = plan.propagate(u0, seed=2)
+    plan.set_config()
+    plan.tune()
+    for kernel in ("row_fwd", "row_bwd"):
+        say(f"[tune] {kernel} n={n} R={r}: {_entry(api, kernel)}")
+        assert [e["batch_class"] for e in _entry(api, kernel)] == classes
+    cfg = plan.config
+    plan.set_config(row_waves=cfg["row_waves"], row_waves_bwd=cfg["row_waves_bwd"])
+    assert torch.equal(plan.propagate(u0, seed=2), ref)
+    plan.close()
+
+
+# above the one-wave line, so that the forward pass is the relay schedule and the
+# adjoint the pair schedule; an odd count leaves the last pair's second half idle
+@pytest.mark.parametrize("n,r", [(256, 34), (512, 11), (1024, 5)])
+def test_hints_keep_the_bits_of_relay_and_pair(api, n, r):
+    plan = api.Plan(_path(n, r, 2, 3))
+    u0 = torch.from_numpy(workloads.seeded_field((n, n), 51)).cuda()
+    g = torch.from_numpy(workloads.seeded_field((r, n, n), 52)).cuda()
+    ref = plan.propagate(u0, seed=2)
+    _, ck = plan.propagate(u0, seed=2, checkpoints=True)
+    ref_in, ref_phi = plan.propagate_backward(g, ck, seed=2)
+    for w in (2, 4):
+        plan.set_config(row_waves=w, row_waves_bwd=w)
+        assert torch.equal(plan.propagate(u0, seed=2), ref)
+        g_in, g_phi = plan.propagate_backward(g, ck, seed=2)
+        assert torch.equal(g_in, ref_in) and torch.equal(g_phi, ref_phi)
+    plan.close()
