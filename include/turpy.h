@@ -554,7 +554,8 @@ typedef struct turpy_launch_config {
  * the strip widths now in the plan (turpy_plan_config has every choice). */
 turpy_status turpy_plan_tune(turpy_plan* plan, uint32_t flags, void* ws, size_t ws_bytes, void* stream,
                              int32_t* col_width, int32_t* synth_width);
-/* The strip widths the plan's launches use now. */
+/* The strip widths the plan's launches use now (a synthesis launch that covers
+ * the last few screens of a path may take narrower strips). */
 turpy_status turpy_plan_widths(const turpy_plan* plan, int32_t* col_width, int32_t* synth_width);
 /* Set the strip widths directly: 0 restores the built-in choice; any other
  * value must be a width built for the plan's N (TURPY_E_INVALID otherwise,

@@ -1363,6 +1363,14 @@ void apply_cached_widths(turpy_plan* pl) {
   if (cached(row_key(pl, TURPY_TUNE_ROW_BWD), &e)) pl->row_waves_bwd = e.waves;
 }
 
+// The built-in widths of a call's full launches.
+int built_in_synth_width(const turpy_plan* pl) {
+  return default_synth_width(pl->n, pl->P * screens_per_launch(pl, TURPY_SCREENS_SYNTH));
+}
+int built_in_ar_width(const turpy_plan* pl) {
+  return default_ar_width(pl->n, pl->P * screens_per_launch(pl, TURPY_SCREENS_SPECTRA));
+}
+
 struct LaunchChoice {
   int width, radix, waves;
 };
@@ -1499,7 +1507,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
     // the first launch of a call: as many screens as one covers
     SynthArgs a = synth_args(pl, 0, 0, 0, wsp.batch, nullptr, wsp);
     a.t_dev = nullptr;
-    if (turpy_status s = tune_key(sk, strip_choices(n), {default_synth_width(n, pl->P * wsp.batch), 0, 0}, st,
+    if (turpy_status s = tune_key(sk, strip_choices(n), {built_in_synth_width(pl), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
                                     a.width = k.width;
                                     a.radix = k.radix;
@@ -1520,7 +1528,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
     a.t_dev = nullptr;
     a.M = wa.batch;
     bool flip = false;
-    if (turpy_status s = tune_key(ak, strip_choices(n), {default_ar_width(n, planes), 0, 0}, st,
+    if (turpy_status s = tune_key(ak, strip_choices(n), {built_in_ar_width(pl), 0, 0}, st,
                                   [&](const LaunchChoice& k) {
                                     a.width = k.width;
                                     a.radix = k.radix;
@@ -1575,7 +1583,7 @@ turpy_status turpy_plan_tune(turpy_plan* pl, uint32_t flags, void* ws, size_t ws
 turpy_status turpy_plan_widths(const turpy_plan* pl, int32_t* col_width, int32_t* synth_width) {
   if (!pl) return fail(TURPY_E_INVALID, "plan_widths: NULL plan");
   if (col_width) *col_width = pl->col_width ? pl->col_width : default_col_width(pl->n, pl->R);
-  if (synth_width) *synth_width = pl->synth_width ? pl->synth_width : default_synth_width(pl->n, pl->P);
+  if (synth_width) *synth_width = pl->synth_width ? pl->synth_width : built_in_synth_width(pl);
   return TURPY_OK;
 }
 
@@ -1593,11 +1601,11 @@ turpy_status turpy_plan_config(const turpy_plan* pl, turpy_launch_config* out) {
   if (!pl || !out) return fail(TURPY_E_INVALID, "plan_config: NULL argument");
   out->col_width = pl->col_width ? pl->col_width : default_col_width(pl->n, pl->R);
   out->col_radix = pl->col_radix;
-  out->synth_width = pl->synth_width ? pl->synth_width : default_synth_width(pl->n, pl->P);
+  out->synth_width = pl->synth_width ? pl->synth_width : built_in_synth_width(pl);
   out->synth_radix = pl->synth_radix;
   out->row_waves = pl->row_waves ? pl->row_waves : 3;
   out->row_waves_bwd = pl->row_waves_bwd ? pl->row_waves_bwd : 3;
-  out->ar_width = pl->ar_width ? pl->ar_width : default_ar_width(pl->n, pl->P);
+  out->ar_width = pl->ar_width ? pl->ar_width : built_in_ar_width(pl);
   out->ar_radix = pl->ar_radix;
   return TURPY_OK;
 }

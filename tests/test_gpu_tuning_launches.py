@@ -124,3 +124,17 @@ def test_hints_keep_the_bits_of_relay_and_pair(api, n, r):
         g_in, g_phi = plan.propagate_backward(g, ck, seed=2)
         assert torch.equal(g_in, ref_in) and torch.equal(g_phi, ref_phi)
     plan.close()
+
+
+# Untuned launches: the widest strip of which every CU has one (512: 8 columns,
+# the AR step 16; 1024: 4 and 16).  One pair, ten screens at once; 1024 takes
+# four screens of a pair to a launch, eight of a single realization
+@pytest.mark.parametrize("n,r,m,synth,ar", [(512, 2, 10, 8, 16), (512, 2, 1, 4, 4), (512, 1, 10, 8, 16),
+                                            (1024, 2, 8, 4, 16), (1024, 2, 1, 4, 4), (256, 2, 20, 16, 16)])
+def test_reported_widths_are_the_launched_ones(api, n, r, m, synth, ar):
+    plan = api.Plan(_path(n, r, m))
+    cfg = plan.config
+    assert (cfg["synth_width"], cfg["ar_width"]) == (synth, ar) and plan.widths["synth"] == synth
+    plan.set_config(**cfg)
+    assert plan.config == cfg
+    plan.close()
