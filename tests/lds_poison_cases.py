@@ -36,8 +36,9 @@ def run_cases():
     def c64(a):
         return torch.from_numpy(np.ascontiguousarray(a, dtype=np.complex64)).cuda()
 
-    # forward, adjoint and screens at every row-pass schedule: row_pass (N <= 32),
-    # pair (checkpoints), relay (N <= 1024), pair at N = 2048
+    # forward, adjoint and screens: row_pass (N <= 32), one wave per transform
+    # (N <= 1024 at these sizes), pair at N = 2048; the relay and pair schedules
+    # below it are in lds_poison_schedules.py
     for n, r, sh, tf in ((16, 3, 0, 0), (64, 3, 3, 1), (256, 4, 3, 0), (1024, 2, 0, 0), (2048, 2, 3, 0)):
         p = _path(workloads, n, 2, r, sh, tf)
         plan = api.Plan(p)
