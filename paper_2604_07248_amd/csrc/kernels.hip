@@ -1736,7 +1736,7 @@ bool trio_pays(const RowArgs& a, int64_t planes) {
 template <int N, int W>
 void relay_launch_w(const RowArgs& a, int64_t pairs, hipStream_t s) {
   constexpr int WB = row_waves_built(N, W) ? W : kRowWaves;
-  const dim3 grid((a.solo ? N / 2 : N) / (2 * relay_rows<N>()), static_cast<uint32_t>(pairs));
+  const dim3 grid(N / (2 * relay_rows<N>()), static_cast<uint32_t>(pairs));
   hipLaunchKernelGGL((row_relay_kernel<N, WB>), grid, dim3(relay_block<N>()), 0, s, a);
 }
 
@@ -1746,7 +1746,7 @@ bool relay_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
     return false;
   } else {
     if (a.screen_mode != ROW_SCRATCH || a.backward || a.conj_tables || a.ckpt_out || a.pre) return false;
-    if (a.solo && 2 * relay_rows<N>() > N / 2) return false;
+    static_assert(trio_takes(N, 1, true), "single realizations run one wave per transform here");
     switch (a.waves ? a.waves : kRowWaves) {
       case 2: relay_launch_w<N, 2>(a, pairs, s); break;
       case 4: relay_launch_w<N, 4>(a, pairs, s); break;
@@ -1777,9 +1777,9 @@ hipError_t row_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
   constexpr int G = row_groups<N>();
   dim3 grid(N / G, static_cast<uint32_t>(pairs));
   dim3 block(row_block<N>());
-  if (a.screen_mode == ROW_NO_SCREEN)
+  if (a.screen_mode == ROW_NO_SCREEN) {
     hipLaunchKernelGGL((row_pass_kernel<N, ROW_NO_SCREEN, false>), grid, block, 0, s, a);
-  else if (trio_pays<N>(a, pairs)) {
+  } else if (trio_pays<N>(a, pairs)) {
     if constexpr (trio_fits(N)) {
       const dim3 tgrid((a.solo ? N / 2 : N) / trio_rows<N>(), static_cast<uint32_t>(pairs)), tblock(trio_block<N>());
       if (a.backward) hipLaunchKernelGGL((row_trio_kernel<N, true>), tgrid, tblock, 0, s, a);
@@ -1791,13 +1791,13 @@ hipError_t row_launch(const RowArgs& a, int64_t pairs, hipStream_t s) {
     if (a.screen_mode == ROW_SCRATCH && !a.backward) {
       if (a.phase_out && a.screen_count > 1) grid.z = static_cast<uint32_t>(a.screen_count);
       hipLaunchKernelGGL((row_pass_kernel<N, ROW_SCRATCH, false>), grid, block, 0, s, a);
-    }
-    else if (a.screen_mode == ROW_SCRATCH)
+    } else if (a.screen_mode == ROW_SCRATCH) {
       hipLaunchKernelGGL((row_pass_kernel<N, ROW_SCRATCH, true>), grid, block, 0, s, a);
-    else if (!a.backward)
+    } else if (!a.backward) {
       hipLaunchKernelGGL((row_pass_kernel<N, ROW_MATERIALIZED, false>), grid, block, 0, s, a);
-    else
+    } else {
       hipLaunchKernelGGL((row_pass_kernel<N, ROW_MATERIALIZED, true>), grid, block, 0, s, a);
+    }
   } else if (relay_launch<N>(a, pairs, s)) {
     // synthesised screens on the relay schedule
   } else {

@@ -27,7 +27,10 @@ constexpr int row_block() { return row_groups<N>() * (N / kE); }
 // A launch over few planes takes narrower strips until it has a block for
 // every CU (n = 512, 4 planes: 16 columns 15.4 us, 8 columns 13.7; n = 1024,
 // one plane of the AR step: 23.0 us for 16 columns, 15.9 for 4), as long as
-// a block keeps a whole wave.
+// a block keeps a whole wave.  A single realization's synthesis launches half
+// the blocks and takes the same line: from n = 128 that is the best width of
+// the three or one within 4 % (n = 512, four screens, us for 4 / 8 / 16 columns
+// 12.9 / 11.3 / 14.1, where counting its own blocks would take 4).
 constexpr int kFillBlocks = 256;
 constexpr int fill_width(int n, int64_t planes, int widest) {
   int k = widest;
