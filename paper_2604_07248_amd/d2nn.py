@@ -21,62 +21,78 @@ from . import binding as B
 
 class _Loss(torch.autograd.Function):
     """The loss and its gradient in two passes over the fields
-    (turpy_receiver_loss)."""
+    (turpy_receiver_loss).  The forward pass leaves its sums and, behind them,
+    the mean intensities in one buffer."""
 
     SUMS = 4 + 4 * 1024
 
     @staticmethod
     def forward(ctx, u_out, i_vac, aperture):
         pixels, batch = i_vac.numel(), u_out.shape[0]
-        mean = torch.empty_like(i_vac)
-        sums = torch.empty(_Loss.SUMS, dtype=torch.float64, device=u_out.device)
+        work = torch.empty(_Loss.SUMS + (pixels + 1) // 2, dtype=torch.float64, device=u_out.device)
         loss = torch.empty((), dtype=torch.float32, device=u_out.device)
-        B.receiver_loss(pixels, batch, api._ptr(u_out), api._ptr(i_vac), api._ptr(aperture), api._ptr(mean),
-                        api._ptr(sums), api._ptr(loss), api._stream())
-        ctx.save_for_backward(u_out, i_vac, aperture, mean, sums)
+        sums = work.data_ptr()
+        B.receiver_loss(pixels, batch, u_out.data_ptr(), i_vac.data_ptr(), aperture.data_ptr(), sums + 8 * _Loss.SUMS,
+                        sums, loss.data_ptr(), _stream(u_out))
+        ctx.save_for_backward(u_out, i_vac, aperture, work)
         return loss
 
     @staticmethod
     def backward(ctx, grad_loss):
-        u_out, i_vac, aperture, mean, sums = ctx.saved_tensors
+        u_out, i_vac, aperture, work = ctx.saved_tensors
         if torch.is_grad_enabled():  # create_graph: a gradient that can be differentiated again
             return torch.autograd.grad(_loss_ops(u_out, i_vac, aperture), u_out, grad_loss, create_graph=True) + \
                 (None, None)
         # batched cotangents (vmap over the backward pass) have no memory of their own, and a
         # dual one has a tangent to carry: the kernel then takes 1, and tensor operations the rest
-        direct = torch._C._has_storage(grad_loss) and \
-            torch.autograd.forward_ad.unpack_dual(grad_loss).tangent is None
-        unit = grad_loss.resolve_neg() if direct else torch.ones((), dtype=torch.float32, device=u_out.device)
-        if _readable(u_out, i_vac, aperture) and _is(mean, i_vac, torch.float32, i_vac.shape) and \
-                _is(sums, i_vac, torch.float64, (_Loss.SUMS,)):
+        direct = torch._C._has_storage(grad_loss) and not _dual(grad_loss)
+        # saved-tensor hooks may hand back other types and layouts than were saved
+        if _readable(u_out, i_vac, aperture) and _plain(work) and work.dtype is torch.float64 and \
+                work.device == u_out.device and work.numel() == _Loss.SUMS + (i_vac.numel() + 1) // 2 and \
+                work.is_contiguous():
+            unit = grad_loss.resolve_neg() if direct else torch.ones((), dtype=torch.float32, device=u_out.device)
             grad_u = torch.empty_like(u_out)
-            B.receiver_loss_backward(i_vac.numel(), u_out.shape[0], api._ptr(u_out), api._ptr(i_vac),
-                                     api._ptr(aperture), api._ptr(mean), api._ptr(sums), api._ptr(unit),
-                                     api._ptr(grad_u), api._stream())
+            sums = work.data_ptr()
+            B.receiver_loss_backward(i_vac.numel(), u_out.shape[0], u_out.data_ptr(), i_vac.data_ptr(),
+                                     aperture.data_ptr(), sums + 8 * _Loss.SUMS, sums, unit.data_ptr(),
+                                     grad_u.data_ptr(), _stream(u_out))
             if direct:
                 return grad_u, None, None
-        else:  # saved-tensor hooks may hand back other types and layouts than were saved
+        else:
             with torch.enable_grad():
                 u_again = u_out.detach().requires_grad_()
                 (grad_u,) = torch.autograd.grad(_loss_ops(u_again, i_vac, aperture), u_again)
         return grad_u * grad_loss, None, None
 
 
-def _is(t, like, dtype, shape):
-    """A plain contiguous tensor of this type and shape on the device of `like`."""
-    return (type(t) in (torch.Tensor, torch.nn.Parameter) and t.device == like.device and t.dtype == dtype
-            and t.shape == tuple(shape) and t.is_contiguous() and not t.is_neg() and not t.is_conj()
-            and torch.autograd.forward_ad.unpack_dual(t).tangent is None)
+def _stream(t):
+    return torch._C._cuda_getCurrentRawStream(t.device.index)
+
+
+_PLAIN = (torch.Tensor, torch.nn.Parameter)
+
+
+def _plain(t):
+    return type(t) in _PLAIN and not t.is_neg() and not _dual(t)
+
+
+def _dual(t):
+    """Whether t carries a forward-mode tangent."""
+    ad = torch.autograd.forward_ad
+    return ad._current_level >= 0 and ad.unpack_dual(t).tangent is not None
 
 
 def _readable(u_out, i_vac, aperture):
     """Whether the library's kernels can read these: contiguous complex64 fields
     and float32 planes on the current GPU, within the sizes they take."""
-    return (type(u_out) in (torch.Tensor, torch.nn.Parameter) and u_out.is_cuda
-            and u_out.device.index == torch.cuda.current_device() and u_out.dim() == 3 and 0 < u_out.numel()
-            and u_out.shape[0] <= 1 << 19 and u_out.numel() <= u_out.shape[0] << 32
-            and _is(u_out, u_out, torch.complex64, u_out.shape)
-            and all(_is(t, u_out, torch.float32, u_out.shape[1:]) for t in (i_vac, aperture)))
+    if not (_plain(u_out) and _plain(i_vac) and _plain(aperture) and u_out.is_cuda):
+        return False
+    shape, device, f32 = u_out.shape, u_out.device, torch.float32
+    return (len(shape) == 3 and i_vac.shape == shape[1:] and aperture.shape == i_vac.shape
+            and 0 < shape[0] <= 1 << 19 and 0 < i_vac.numel() <= 1 << 32
+            and u_out.dtype is torch.complex64 and i_vac.dtype is f32 and aperture.dtype is f32
+            and i_vac.device == device and aperture.device == device and device.index == torch.cuda.current_device()
+            and u_out.is_contiguous() and i_vac.is_contiguous() and aperture.is_contiguous() and not u_out.is_conj())
 
 
 def _fused(u_out, i_vac, aperture):
@@ -88,7 +104,7 @@ def _fused(u_out, i_vac, aperture):
         return False
     if torch.overrides._get_current_function_mode_stack() or torch.utils._python_dispatch._get_current_dispatch_mode():
         return False
-    return _readable(u_out, i_vac, aperture) and not (i_vac.requires_grad or aperture.requires_grad)
+    return not (i_vac.requires_grad or aperture.requires_grad) and _readable(u_out, i_vac, aperture)
 
 
 def loss_fn(u_out, i_vac, aperture):
