@@ -1641,11 +1641,12 @@ __global__ __launch_bounds__(kFinThreads) void finalize_summary_kernel(FinalizeA
 
 __global__ __launch_bounds__(256) void finalize_map_kernel(FinalizeArgs a) {
   const int64_t np = static_cast<int64_t>(a.n) * a.n;
-  const int64_t p = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= np) return;
-  const double m1 = (static_cast<double>(a.moments[p]) - a.moments[np + p]) / a.count;
-  const double m2 = (static_cast<double>(a.moments[2 * np + p]) - a.moments[3 * np + p]) / a.count;
-  a.si_map[p] = static_cast<float>(m2 / (m1 * m1) - 1.0);
+  for (int64_t p = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x; p < np;
+       p += static_cast<int64_t>(gridDim.x) * 256) {
+    const double m1 = (static_cast<double>(a.moments[p]) - a.moments[np + p]) / a.count;
+    const double m2 = (static_cast<double>(a.moments[2 * np + p]) - a.moments[3 * np + p]) / a.count;
+    a.si_map[p] = static_cast<float>(m2 / (m1 * m1) - 1.0);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -2198,7 +2199,7 @@ hipError_t launch_finalize(const FinalizeArgs& a, hipStream_t s) {
     for (int q = 0; q < kFinPasses; ++q) hipLaunchKernelGGL(finalize_bracket_kernel, grid, block, 0, s, a, w, q);
   hipLaunchKernelGGL(finalize_region_kernel, grid, block, 0, s, a, w);
   hipLaunchKernelGGL(finalize_summary_kernel, dim3(1), block, 0, s, a, w);
-  hipLaunchKernelGGL(finalize_map_kernel, dim3(static_cast<uint32_t>((np + 255) / 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(finalize_map_kernel, dim3(plane_blocks(np, 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 

@@ -131,6 +131,14 @@ __host__ __device__ constexpr int sh_slot(int n, int i) {
 // (SynthArgs::solo): the row passes' halves must be whole waves on N/2 rows.
 constexpr bool solo_fits(int n) { return n >= 64; }
 
+// Blocks of `threads` for a pass over a plane of up to 2^32 pixels: one pixel a
+// thread while a launch allows that many threads in x (fewer than 2^32).
+constexpr uint32_t plane_blocks(int64_t pixels, int threads) {
+  const int64_t b = (pixels + threads - 1) / threads, most = (int64_t(1) << 32) / threads - 1;
+  return static_cast<uint32_t>(b < most ? b : most);
+}
+static_assert(plane_blocks(int64_t(1) << 32, 256) * int64_t(256) < int64_t(1) << 32, "one launch covers 2^32 pixels");
+
 // Spread a 1-D block index so that consecutive logical tiles land on the same
 // XCD (blocks are dealt round-robin over the 8 XCDs, each with its own L2).
 __device__ __forceinline__ uint32_t xcd_remap(uint32_t b, uint32_t nb) {

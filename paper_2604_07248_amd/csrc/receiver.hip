@@ -384,16 +384,8 @@ hipError_t launch_loss(const LossArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Blocks of the adjoint along the pixels: one pixel a thread while a launch
-// allows that many threads in x (fewer than 2^32), more beyond.
-constexpr int64_t loss_grad_blocks(int64_t pixels) {
-  const int64_t b = (pixels + kLossThreads - 1) / kLossThreads, most = (int64_t(1) << 32) / kLossThreads - 1;
-  return b < most ? b : most;
-}
-static_assert(loss_grad_blocks(int64_t(1) << 32) * kLossThreads < int64_t(1) << 32, "one launch covers 2^32 pixels");
-
 hipError_t launch_loss_grad(const LossArgs& a, hipStream_t s) {
-  const dim3 grid(static_cast<uint32_t>(loss_grad_blocks(a.pixels)),
+  const dim3 grid(plane_blocks(a.pixels, kLossThreads),
                   static_cast<uint32_t>((a.batch + kLossChunk - 1) / kLossChunk));
   hipLaunchKernelGGL(loss_grad_kernel, grid, dim3(kLossThreads), 0, s, a);
   return hipGetLastError();
