@@ -305,8 +305,12 @@ turpy_status turpy_propagate_backward_reversible(turpy_plan* plan, uint64_t seed
  *  compensated sums of the non-empty chunks join the stored ones in chunk
  *  order: a fixed order for a given (n, batch), bitwise reproducible.
  *  If finalize != 0: with count = total realizations accumulated and
- *  m = sums / count, write si_map float [n][n] = m2/m1^2 - 1 (may be NULL)
- *  and summary double[8] (device):
+ *  m = sums / count, write si_map float [n][n] = m2/m1^2 - 1 and summary
+ *  double[8] (device).  si_map may be NULL, but the call is faster with one:
+ *  from n = 64 on, a map at an 8-byte boundary holds the partial sums of many
+ *  blocks until it is written; without it one block adds everything up
+ *  (n = 1024 with a power cutoff: 0.11 ms against 14 ms).  The map must not
+ *  overlap the other arrays.  The summary:
  *    [0] SI averaged over the region, weighted: sum w SI / sum w;
  *    [1] W_2nd = sqrt(2 sum r^2 m1 / sum m1);
  *    [2] W_fit, least-squares fit of ln m1 = a - 2 r^2/W^2 over m1 >= e^-2 max m1;
